@@ -132,6 +132,15 @@ int mfpsn_forward(const mfpsn_desc* desc, const void* x, const int8_t* sign, con
                   const void* bias, const void* v_th_c, uint8_t* spikes, void* h_out, void* sg_out,
                   void* stream);
 
+/* mfpsn_forward with the spikes in the storage type of desc->dtype instead of
+ * bytes: 1.0f, bfloat16 1.0 or int16 256 (Q8.8 1.0) where H >= V_th[c], else
+ * 0 (what mfpsn_spikes_to_input makes of mfpsn_forward's spikes).
+ *   spikes : [T][N][C][S] storage type, aligned to its element size
+ * Everything else as mfpsn_forward. */
+int mfpsn_forward_values(const mfpsn_desc* desc, const void* x, const int8_t* sign, const int8_t* shift,
+                         const void* bias, const void* v_th_c, void* spikes, void* h_out, void* sg_out,
+                         void* stream);
+
 /* Bytes of device workspace mfpsn_backward needs for this problem (per-block
  * partial sums of grad_w and grad_b: double, or int64 for Q8.8).  Returns a
  * status; *bytes is written on success. */

@@ -112,12 +112,13 @@ bool pair_aligned(std::initializer_list<const void*> ptrs)
 // The flat forward (16- or 8-byte accesses over the flattened rows): an
 // order it is built for, S a multiple of its columns per lane, and tensors
 // aligned for its accesses.
-int flat_layout(const mfpsn_desc* d, const void* x, const void* spikes, const void* h_out, const void* sg_out)
+int flat_layout(const mfpsn_desc* d, const void* x, const void* spikes, int spike_es, const void* h_out,
+                const void* sg_out)
 {
     const int nv = flat_nv(d->k, d->dtype);
     if (nv == 0 || d->S % nv != 0)
         return 0;
-    const uintptr_t wx = (uintptr_t)nv * elem_bytes(d->dtype), ws = (uintptr_t)nv;
+    const uintptr_t wx = (uintptr_t)nv * elem_bytes(d->dtype), ws = (uintptr_t)nv * spike_es;
     const uintptr_t ww = 4u * nv < 16u ? 4u * nv : 16u;
     if (((uintptr_t)x % wx) != 0 || ((uintptr_t)spikes % ws) != 0 || ((uintptr_t)h_out % ww) != 0 ||
         ((uintptr_t)sg_out % ww) != 0)
@@ -248,6 +249,41 @@ size_t backward_workspace(const mfpsn_desc* d)
     return b;
 }
 
+// The forward with its spikes as bytes (spike_es = 1) or as values of the
+// storage type (spike_es = its element size); desc is valid
+int forward_spikes(const mfpsn_desc* desc, const void* x, const int8_t* sign, const int8_t* shift, const void* bias,
+                   const void* v_th_c, void* spikes, int spike_es, void* h_out, void* sg_out, void* stream)
+{
+    const int64_t total = (int64_t)desc->T * desc->N * desc->C * desc->S;
+    if (total > 0 && (!x || !spikes))
+        return MFPSN_ERR_NULL;
+    if (desc->C > 0 && (!sign || !shift || !bias))
+        return MFPSN_ERR_NULL;
+    if (!aligned(x, elem_bytes(desc->dtype)) || !aligned(bias, 4) || !aligned(v_th_c, 4) ||
+        !aligned(h_out, 4) || !aligned(sg_out, 4) || !aligned(spikes, spike_es))
+        return MFPSN_ERR_ALIGN;
+    if (total == 0)
+        return MFPSN_OK;
+    FwdArgs a;
+    a.g = plan(desc, false, pair_layout(desc) && pair_aligned({x, spikes, h_out, sg_out}) ? 2 : 1,
+               flat_layout(desc, x, spikes, spike_es, h_out, sg_out),
+               h_out || sg_out ? 4 : elem_bytes(desc->dtype));
+    if (a.g.items > kMaxItems)
+        return MFPSN_ERR_SHAPE;
+    a.x = x;
+    a.sign = sign;
+    a.shift = shift;
+    a.bias = bias;
+    a.v_th_c = v_th_c;
+    a.spikes = spikes;
+    a.spike_es = spike_es;
+    a.h_out = h_out;
+    a.sg_out = sg_out;
+    if (launch_forward(a, desc->dtype, (hipStream_t)stream) != hipSuccess)
+        return MFPSN_ERR_HIP;
+    return MFPSN_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -280,36 +316,19 @@ int mfpsn_forward(const mfpsn_desc* desc, const void* x, const int8_t* sign, con
                   const void* bias, const void* v_th_c, uint8_t* spikes, void* h_out, void* sg_out,
                   void* stream)
 {
-    int st = validate(desc);
+    const int st = validate(desc);
     if (st != MFPSN_OK)
         return st;
-    const int64_t total = (int64_t)desc->T * desc->N * desc->C * desc->S;
-    if (total > 0 && (!x || !spikes))
-        return MFPSN_ERR_NULL;
-    if (desc->C > 0 && (!sign || !shift || !bias))
-        return MFPSN_ERR_NULL;
-    if (!aligned(x, elem_bytes(desc->dtype)) || !aligned(bias, 4) || !aligned(v_th_c, 4) ||
-        !aligned(h_out, 4) || !aligned(sg_out, 4))
-        return MFPSN_ERR_ALIGN;
-    if (total == 0)
-        return MFPSN_OK;
-    FwdArgs a;
-    a.g = plan(desc, false, pair_layout(desc) && pair_aligned({x, spikes, h_out, sg_out}) ? 2 : 1,
-               flat_layout(desc, x, spikes, h_out, sg_out),
-               h_out || sg_out ? 4 : elem_bytes(desc->dtype));
-    if (a.g.items > kMaxItems)
-        return MFPSN_ERR_SHAPE;
-    a.x = x;
-    a.sign = sign;
-    a.shift = shift;
-    a.bias = bias;
-    a.v_th_c = v_th_c;
-    a.spikes = spikes;
-    a.h_out = h_out;
-    a.sg_out = sg_out;
-    if (launch_forward(a, desc->dtype, (hipStream_t)stream) != hipSuccess)
-        return MFPSN_ERR_HIP;
-    return MFPSN_OK;
+    return forward_spikes(desc, x, sign, shift, bias, v_th_c, spikes, 1, h_out, sg_out, stream);
+}
+
+int mfpsn_forward_values(const mfpsn_desc* desc, const void* x, const int8_t* sign, const int8_t* shift,
+                         const void* bias, const void* v_th_c, void* spikes, void* h_out, void* sg_out, void* stream)
+{
+    const int st = validate(desc);
+    if (st != MFPSN_OK)
+        return st;
+    return forward_spikes(desc, x, sign, shift, bias, v_th_c, spikes, elem_bytes(desc->dtype), h_out, sg_out, stream);
 }
 
 int mfpsn_backward_workspace_size(const mfpsn_desc* desc, size_t* bytes)

@@ -136,7 +136,8 @@ struct FwdArgs {
     const int8_t* shift;
     const void* bias;
     const void* v_th_c;  // nullable: per-channel thresholds, float or int32 [C]
-    uint8_t* spikes;
+    void* spikes;      // bytes 0 / 1, or 0 and 1 in the storage type (spike_es)
+    int32_t spike_es;  // bytes per spike: 1, or the storage type's (spikes as the next layer's input)
     void* h_out;       // nullable: potentials H
     void* sg_out;      // nullable: surrogate factor of H
 };

@@ -55,6 +55,8 @@ _P = ctypes.c_void_p
 _DP = ctypes.POINTER(MfpsnDesc)
 _lib.mfpsn_forward.argtypes = [_DP, _P, _P, _P, _P, _P, _P, _P, _P, _P]
 _lib.mfpsn_forward.restype = ctypes.c_int
+_lib.mfpsn_forward_values.argtypes = _lib.mfpsn_forward.argtypes
+_lib.mfpsn_forward_values.restype = ctypes.c_int
 _lib.mfpsn_backward_workspace_size.argtypes = [_DP, ctypes.POINTER(ctypes.c_size_t)]
 _lib.mfpsn_backward_workspace_size.restype = ctypes.c_int
 _lib.mfpsn_backward.argtypes = [_DP, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, ctypes.c_size_t, _P]
@@ -151,6 +153,13 @@ def mfpsn_forward(desc: MfpsnDesc, x, sign, shift, bias, v_th_c, spikes, h_out=N
                   stream=None) -> None:
     _check(_lib.mfpsn_forward(ctypes.byref(desc), _ptr(x), _ptr(sign), _ptr(shift), _ptr(bias), _ptr(v_th_c),
                               _ptr(spikes), _ptr(h_out), _ptr(sg_out), _stream(stream)), "mfpsn_forward")
+
+
+def mfpsn_forward_values(desc: MfpsnDesc, x, sign, shift, bias, v_th_c, spikes, h_out=None, sg_out=None,
+                         stream=None) -> None:
+    _check(_lib.mfpsn_forward_values(ctypes.byref(desc), _ptr(x), _ptr(sign), _ptr(shift), _ptr(bias), _ptr(v_th_c),
+                                     _ptr(spikes), _ptr(h_out), _ptr(sg_out), _stream(stream)),
+           "mfpsn_forward_values")
 
 
 def mfpsn_backward_workspace_size(desc: MfpsnDesc) -> int:
@@ -264,18 +273,19 @@ def _expect(t, dtype, device, name):
 
 
 def forward(desc: MfpsnDesc, x, sign, shift, bias, want_h: bool = False, want_sg: bool = False, stream=None,
-            v_th_c=None):
+            v_th_c=None, values: bool = False):
     """spikes, plus H (want_h) and the surrogate factor (want_sg) in that order.
-    v_th_c: optional per-channel thresholds [C] (float, int32 for Q8.8)."""
+    v_th_c: optional per-channel thresholds [C] (float, int32 for Q8.8).
+    values: spikes in x's storage type (1 is 256 in Q8.8) instead of bytes."""
     dev = x.device
     _expect(x, STORAGE[desc.dtype], dev, "x")
     _expect(bias, BIAS[desc.dtype], dev, "bias")
     if v_th_c is not None:
         _expect(v_th_c, BIAS[desc.dtype], dev, "v_th_c")
-    spikes = torch.empty(x.shape, dtype=torch.uint8, device=dev)
+    spikes = torch.empty(x.shape, dtype=x.dtype if values else torch.uint8, device=dev)
     h = torch.empty(x.shape, dtype=H_OUT[desc.dtype], device=dev) if want_h else None
     sg = torch.empty(x.shape, dtype=SG_OUT[desc.dtype], device=dev) if want_sg else None
-    mfpsn_forward(desc, x, sign, shift, bias, v_th_c, spikes, h, sg, stream)
+    (mfpsn_forward_values if values else mfpsn_forward)(desc, x, sign, shift, bias, v_th_c, spikes, h, sg, stream)
     out = (spikes,) + ((h,) if want_h else ()) + ((sg,) if want_sg else ())
     return out if len(out) > 1 else spikes
 
@@ -454,11 +464,11 @@ class MfPSNFunction(torch.autograd.Function):
         wc = w.detach().contiguous()
         sign, shift = quantize(wc, shift_lo, shift_hi)
         xc = x.detach().contiguous()
-        spikes, sg = forward(desc, xc, sign, shift, bc, want_sg=True, v_th_c=vc)
+        spikes, sg = forward(desc, xc, sign, shift, bc, want_sg=True, v_th_c=vc, values=True)
         ctx.save_for_backward(xc, wc, sign, shift, bc, sg, vc)
         ctx.desc, ctx.per_channel, ctx.ste = desc, per_channel, ste
         ctx.shift_range = (shift_lo, shift_hi)
-        return spikes.to(x.dtype)
+        return spikes
 
     @staticmethod
     def backward(ctx, grad_spikes):
@@ -488,10 +498,10 @@ class MfPSNBNFunction(torch.autograd.Function):
         w_f, b_f, aux = bn_forward_stats(desc, xc, wc, gamma.detach().contiguous(), beta.detach().contiguous(),
                                          eps, ws)
         sign, shift = quantize(w_f, shift_lo, shift_hi)
-        spikes, sg = forward(desc, xc, sign, shift, b_f, want_sg=True)
+        spikes, sg = forward(desc, xc, sign, shift, b_f, want_sg=True, values=True)
         ctx.save_for_backward(xc, wc, sign, shift, b_f, sg, aux)
         ctx.desc, ctx.eps, ctx.ws = desc, eps, ws
-        return spikes.to(x.dtype)
+        return spikes
 
     @staticmethod
     def backward(ctx, grad_spikes):
