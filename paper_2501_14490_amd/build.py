@@ -38,6 +38,7 @@ HOST_FLAGS = ["-O2", "-std=c++20", "-fPIC", "-Wall", "-Wextra", "-D__HIP_PLATFOR
               "-I/opt/rocm/include"]
 
 K_RANGES = [(1, 8), (9, 12), (13, 16), (17, 20), (21, 23), (24, 26), (27, 29), (30, 31), (32, 32)]
+TILE_K_RANGES = [(1, 8), (9, 16), (17, 24), (25, 32)]  # kTileKs in mfpsn_tl.h
 DTYPES = [0, 1, 2]  # f32, bf16, q8.8
 
 
@@ -64,13 +65,23 @@ def _units():
     units.append((obj, [HIPCC, *DEVICE_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", "-c", qg_src, "-o", obj],
                   [qg_src, os.path.join(CSRC, "mfpsn_qgrad.h")]))
     tl_src = os.path.join(CSRC, "mfpsn_tl.hip")
-    tl_deps = [tl_src, os.path.join(CSRC, "mfpsn_tl.h"), os.path.join(CSRC, "mfpsn_surrogate.h"),
+    tl_deps = [tl_src, os.path.join(CSRC, "mfpsn_tl.h"), os.path.join(CSRC, "mfpsn_tl_tile.h"), os.path.join(CSRC, "mfpsn_surrogate.h"),
                os.path.join(INCLUDE, "mfpsn.h")]
     for tag, flag in (("d0", "-DMFPSN_TL_DTYPE=0"), ("d1", "-DMFPSN_TL_DTYPE=1"), ("d2", "-DMFPSN_TL_DTYPE=2"),
                       ("dispatch", None)):
         obj = os.path.join(BUILD, f"tl_{tag}.o")
         units.append((obj, [HIPCC, *DEVICE_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", *([flag] if flag else []),
                             "-c", tl_src, "-o", obj], tl_deps))
+    tile_src = os.path.join(CSRC, "mfpsn_tl_tile.hip")
+    tile_deps = [tile_src, os.path.join(CSRC, "mfpsn_tl_tile.h"), *tl_deps[1:]]
+    obj = os.path.join(BUILD, "tl_tile_dispatch.o")
+    units.append((obj, [HIPCC, *DEVICE_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", "-c", tile_src, "-o", obj], tile_deps))
+    for dt in DTYPES:
+        for lo, hi in TILE_K_RANGES:
+            obj = os.path.join(BUILD, f"tl_tile_d{dt}_k{lo}-{hi}.o")
+            units.append((obj, [HIPCC, *DEVICE_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", f"-DMFPSN_TILE_DTYPE={dt}",
+                                f"-DMFPSN_TILE_KLO={lo}", f"-DMFPSN_TILE_KHI={hi}", "-c", tile_src, "-o", obj],
+                          tile_deps))
     chain_src = os.path.join(CSRC, "mfpsn_chain.hip")
     obj = os.path.join(BUILD, "chain.o")
     units.append((obj, [HIPCC, *DEVICE_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", "-c", chain_src, "-o", obj],
@@ -92,7 +103,8 @@ def _units():
         units.append((obj, ["g++", *HOST_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", "-c", cpp, "-o", obj],
                       [cpp, os.path.join(CSRC, "mfpsn_stream.h"), os.path.join(CSRC, "mfpsn_qgrad.h"),
                        os.path.join(CSRC, "mfpsn_bn.h"), os.path.join(CSRC, "mfpsn_validate.h"),
-                       os.path.join(CSRC, "mfpsn_chain.h"), os.path.join(CSRC, "mfpsn_tl.h"), *api_headers]))
+                       os.path.join(CSRC, "mfpsn_chain.h"), os.path.join(CSRC, "mfpsn_tl.h"),
+                       os.path.join(CSRC, "mfpsn_tl_tile.h"), *api_headers]))
     return units
 
 

@@ -110,6 +110,9 @@ void fast_range(const mfpsn_desc* desc, float* lo, float* hi)
         *hi = emax == 254 ? INFINITY : ldexpf(1.0f, emax - 126);
     }
 }
+
+// Every stored input has exact tap products (as Geom::x_exact)
+int x_exact(const mfpsn_desc* d) { return d->dtype == MFPSN_BF16 && d->shift_lo >= 0 && d->shift_hi <= 16; }
 }  // namespace
 
 int mfpsn_bn_workspace_size(const mfpsn_desc* desc, size_t* bytes)
@@ -283,13 +286,7 @@ int mfpsn_forward_time_last(const mfpsn_desc* desc, const void* x, const int8_t*
     if (st != MFPSN_OK)
         return st;
     const int64_t M = (int64_t)desc->N * desc->C * desc->S;
-    // long columns with histories of at most kTlBwdMaxSpan steps: segments of
-    // 256 steps (1024 for histories above 64); longer histories: segments of
-    // 256 time steps, or of 64 for short sequences (fewer idle lanes)
     const int64_t span = (int64_t)(desc->k - 1) * desc->dilation;
-    const int seg = desc->T > kTlColsMaxT && span <= kTlBwdMaxSpan ? (span > 64 ? kTlBwdSegLong : kTlBwdSeg) : 0;
-    const int spl = desc->T > 96 ? 4 : 1;
-    const int64_t nseg = seg > 0 ? ((int64_t)desc->T + seg - 1) / seg : ((int64_t)desc->T + 64 * spl - 1) / (64 * spl);
     if (M * (((int64_t)desc->T + 63) / 64) >= ((int64_t)1 << 33))  // segments must fit the grid
         return MFPSN_ERR_SHAPE;
     if (M == 0 || desc->T == 0)
@@ -312,19 +309,26 @@ int mfpsn_forward_time_last(const mfpsn_desc* desc, const void* x, const int8_t*
     a.S = desc->S;
     a.k = desc->k;
     a.d = desc->dilation;
-    a.steps_per_lane = spl;
-    a.seg = seg;
-    a.nseg = (int32_t)nseg;
+    // tl_fwd_kernel (histories no tile holds): segments of 256 time steps, or
+    // of 64 for short sequences (fewer idle lanes)
+    a.steps_per_lane = desc->T > 96 ? 4 : 1;
+    a.nseg = (int32_t)(((int64_t)desc->T + 64 * a.steps_per_lane - 1) / (64 * a.steps_per_lane));
     a.halo = span <= kTlMaxHalo ? (int32_t)span : 0;
     a.shift_lo = desc->shift_lo;
     a.shift_hi = desc->shift_hi;
     a.v_th = desc->v_th;
     a.v_th_q = desc->v_th_q;
     fast_range(desc, &a.fast_lo, &a.fast_hi);
-    a.tdiv = desc->T >= 2 ? (uint32_t)((((uint64_t)1) << 32) / (uint64_t)desc->T + 1) : 0;
-    a.vec_x = aligned(x, 4 * es) ? 1 : 0;
+    a.vec_x = aligned(x, 16) ? 1 : 0;
     a.vec_s = aligned(spikes, 16) ? 1 : 0;
-    if (launch_forward_time_last(a, desc->dtype, (hipStream_t)stream) != hipSuccess)
+    a.x_exact = x_exact(desc);
+    TileGeom g;
+    const bool tiles = tile_plan(g, desc->T, desc->N, desc->C, desc->S, desc->k, desc->dilation, es, -1);
+    if (tiles && g.Z >= (int64_t)1 << 31)
+        return MFPSN_ERR_SHAPE;  // (more elements than any memory holds)
+    const hipStream_t s = (hipStream_t)stream;
+    if ((tiles ? launch_forward_tiles(a, g, desc->dtype, s) : launch_forward_time_last(a, desc->dtype, s)) !=
+        hipSuccess)
         return MFPSN_ERR_HIP;
     return MFPSN_OK;
 }
@@ -334,9 +338,7 @@ int mfpsn_forward_time_last(const mfpsn_desc* desc, const void* x, const int8_t*
 static size_t tl_bwd_workspace(const mfpsn_desc* desc)
 {
     const int64_t M = (int64_t)desc->N * desc->C * desc->S;
-    const int seg = (int64_t)(desc->k - 1) * desc->dilation > 64 ? kTlBwdSegLong : kTlBwdSeg;
-    const int64_t nseg = ((int64_t)desc->T + seg - 1) / seg;
-    const int64_t slots = tl_bwd_slots(M, desc->T, desc->C, desc->N, nseg);
+    const int64_t slots = tl_bwd_slots(M, desc->T, desc->C, desc->N, (int64_t)(desc->k - 1) * desc->dilation);
     return (size_t)(desc->k + 1) * ((size_t)desc->C + (size_t)slots) * 8;
 }
 
@@ -359,14 +361,12 @@ int mfpsn_backward_time_last(const mfpsn_desc* desc, const void* x, const void* 
     if (st != MFPSN_OK)
         return st;
     const int64_t M = (int64_t)desc->N * desc->C * desc->S;
-    // long histories: longer segments, so that the dH recomputed over the
-    // history after each segment is a smaller share of its work
-    const int seg = (int64_t)(desc->k - 1) * desc->dilation > 64 ? kTlBwdSegLong : kTlBwdSeg;
+    const int64_t span = (int64_t)(desc->k - 1) * desc->dilation;
+    const int seg = span > 64 ? kTlSegLong : kTlSeg;
     const int64_t nseg = ((int64_t)desc->T + seg - 1) / seg;
     if (M >= ((int64_t)1 << 37))
         return MFPSN_ERR_SHAPE;
-    if (desc->T > kTlColsMaxT &&
-        ((int64_t)(desc->k - 1) * desc->dilation > kTlBwdMaxSpan || M * nseg >= ((int64_t)1 << 33)))
+    if (desc->T > kTlShortT && (span > kTileMaxSpan || M * nseg >= ((int64_t)1 << 33)))
         return MFPSN_ERR_SHAPE;
     const int64_t total = M * desc->T;
     if (total > 0 && (!x || !grad_spikes || !grad_x))
@@ -396,8 +396,7 @@ int mfpsn_backward_time_last(const mfpsn_desc* desc, const void* x, const void* 
     a.shift = shift;
     a.bias = bias;
     a.grad_x = grad_x;
-    a.acc = workspace;
-    a.part = (char*)workspace + (size_t)(desc->k + 1) * (size_t)desc->C * 8;
+    a.part = workspace;
     a.M = M;
     a.T = desc->T;
     a.C = desc->C;
@@ -411,18 +410,24 @@ int mfpsn_backward_time_last(const mfpsn_desc* desc, const void* x, const void* 
     a.sg = desc->surrogate;
     a.alpha = desc->alpha;
     fast_range(desc, &a.fast_lo, &a.fast_hi);
-    a.tdiv = desc->T >= 2 ? (uint32_t)((((uint64_t)1) << 32) / (uint64_t)desc->T + 1) : 0;
-    a.vec_x = aligned(x, 4 * es) && aligned(grad_spikes, 4 * es) ? 1 : 0;
-    a.seg = seg;
-    a.nseg = (int32_t)nseg;
+    a.vec_x = aligned(x, 16) && aligned(grad_spikes, 16) && aligned(grad_x, 16) ? 1 : 0;
+    a.x_exact = x_exact(desc);
     a.chunk = 0;
     hipStream_t s = (hipStream_t)stream;
-    if (launch_backward_time_last(a, desc->dtype, s) != hipSuccess)
-        return MFPSN_ERR_HIP;
-    FinArgs f;
+    if (total > 0) {
+        const int64_t slots = tl_bwd_slots(M, desc->T, desc->C, desc->N, span);
+        TileGeom g;
+        if (!tile_plan(g, desc->T, desc->N, desc->C, desc->S, desc->k, desc->dilation, es, slots) ||
+            g.Z >= (int64_t)1 << 31)
+            return MFPSN_ERR_SHAPE;  // (a plan exists for every accepted call; Z: more elements than any memory holds)
+        if (launch_backward_tiles(a, g, slots, desc->dtype, grad_w, grad_b, s) != hipSuccess)
+            return MFPSN_ERR_HIP;
+        return MFPSN_OK;
+    }
+    FinArgs f;  // an empty sequence: zero sums
     f.C = desc->C;
     f.k = desc->k;
-    f.blocks = 1;
+    f.blocks = 0;
     f.dtype = desc->dtype;
     f.partial = (const double*)workspace;
     f.grad_w = grad_w;

@@ -37,7 +37,12 @@ hipError_t launch_spikes_to_input(const uint8_t*, int64_t, int32_t, void*, hipSt
     return hipSuccess;
 }
 hipError_t launch_forward_time_last(const TlArgs&, int, hipStream_t) { ++stub_launches; return hipSuccess; }
-hipError_t launch_backward_time_last(const TlBwdArgs&, int, hipStream_t) { ++stub_launches; return hipSuccess; }
+hipError_t launch_forward_tiles(const TlArgs&, const TileGeom&, int, hipStream_t) { ++stub_launches; return hipSuccess; }
+hipError_t launch_backward_tiles(TlBwdArgs&, const TileGeom&, int64_t, int, void*, void*, hipStream_t)
+{
+    ++stub_launches;
+    return hipSuccess;
+}
 size_t bn_workspace_bytes(const BnGeom& g) { return ((size_t)2 * g.C + 64) * sizeof(double); }
 hipError_t launch_bn_forward_stats(const BnGeom&, const float*, const float*, const float*, const float*, float,
                                    float*, float*, double*, double*, void*, hipStream_t)
