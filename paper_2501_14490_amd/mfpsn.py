@@ -441,6 +441,24 @@ class StreamState:
         return (spikes, h) if want_h else spikes
 
 
+# Orders up to which the autograd functions let the backward recompute the
+# surrogate factor from x instead of saving it (4 bytes per element written by
+# the forward and read back).  Forward + backward on MI355X, recompute / saved,
+# at orders 8, 12, 16, 24: f32 planes [30,16,64,44,44] 0.70, 0.83, 0.88, 1.03
+# and channels [250,128,512] 0.76, 0.83, 1.04, 1.15 (0.93 at order 16 where the
+# tensors leave the last-level cache, [250,256,512]); bf16 0.70, 0.94, 0.97,
+# 1.06 and 0.85, 0.87, 1.20, 1.14.
+RECOMPUTE_MAX_K = {MFPSN_F32: 16, MFPSN_BF16: 12}
+
+
+def _forward_for_backward(desc, x, sign, shift, bias, v_th_c=None):
+    """Spikes in x's type, and the surrogate factor where the backward wants it
+    saved (else None)."""
+    if desc.k <= RECOMPUTE_MAX_K[desc.dtype]:
+        return forward(desc, x, sign, shift, bias, v_th_c=v_th_c, values=True), None
+    return forward(desc, x, sign, shift, bias, want_sg=True, v_th_c=v_th_c, values=True)
+
+
 class MfPSNFunction(torch.autograd.Function):
     """spikes = Theta(conv_{Q(W)}(x) + b - V_th) with the surrogate-gradient
     backward (Sec. 4.2, App. A.3).  Float storage paths (f32, bf16).
@@ -464,7 +482,7 @@ class MfPSNFunction(torch.autograd.Function):
         wc = w.detach().contiguous()
         sign, shift = quantize(wc, shift_lo, shift_hi)
         xc = x.detach().contiguous()
-        spikes, sg = forward(desc, xc, sign, shift, bc, want_sg=True, v_th_c=vc, values=True)
+        spikes, sg = _forward_for_backward(desc, xc, sign, shift, bc, vc)
         ctx.save_for_backward(xc, wc, sign, shift, bc, sg, vc)
         ctx.desc, ctx.per_channel, ctx.ste = desc, per_channel, ste
         ctx.shift_range = (shift_lo, shift_hi)
@@ -498,7 +516,7 @@ class MfPSNBNFunction(torch.autograd.Function):
         w_f, b_f, aux = bn_forward_stats(desc, xc, wc, gamma.detach().contiguous(), beta.detach().contiguous(),
                                          eps, ws)
         sign, shift = quantize(w_f, shift_lo, shift_hi)
-        spikes, sg = forward(desc, xc, sign, shift, b_f, want_sg=True, values=True)
+        spikes, sg = _forward_for_backward(desc, xc, sign, shift, b_f)
         ctx.save_for_backward(xc, wc, sign, shift, b_f, sg, aux)
         ctx.desc, ctx.eps, ctx.ws = desc, eps, ws
         return spikes
