@@ -1,5 +1,6 @@
-// Internal interface of the time-last kernels (mfpsn_tl.hip: forward and
-// backward) for the C-ABI layer.  Not installed; not part of the ABI.
+// Internal interface of the time-last kernels for the C-ABI layer: the tiles of
+// mfpsn_tl_tile.hip, and the forward for the longest histories (mfpsn_tl.hip).
+// Not installed; not part of the ABI.
 #pragma once
 
 #include <hip/hip_runtime_api.h>
