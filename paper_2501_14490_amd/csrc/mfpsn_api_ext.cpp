@@ -55,43 +55,7 @@ int validate_bn(const mfpsn_desc* d, BnGeom* g)
     g->M = (size_t)d->N * d->C * d->S;
     g->tq = d->T / d->dilation;
     g->tr = d->T % d->dilation;
-    // Walk plan: a grid of about three waves per SIMD (256 CUs x 4 SIMDs),
-    // chunks of each residue class such that each thread has two or three
-    // items (each chunk at least 2k steps), and a thread count that spreads
-    // the items evenly and keeps every thread in one channel
-    constexpr int64_t kTarget = 256 * 4 * 3 * 64;
-    const int64_t L = ((int64_t)d->T + d->dilation - 1) / d->dilation;
-    const int64_t walks = (int64_t)g->M * d->dilation;
-    int64_t nch = walks > 0 ? (2 * kTarget + walks - 1) / walks : 1;
-    const int64_t max_nch = L / (2 * (int64_t)d->k);
-    if (nch > max_nch)
-        nch = max_nch;
-    if (nch < 1)
-        nch = 1;
-    g->lc = L > 0 ? (int32_t)((L + nch - 1) / nch) : 1;  // an empty sequence has no chunks
-    g->nch = (int32_t)((L + g->lc - 1) / g->lc);
-    g->items = (size_t)g->nch * d->dilation * g->M;
-    const int64_t SC = (int64_t)d->S * d->C;
-    int64_t a = SC, b = kBnThreads;  // base = lcm(SC, block size)
-    while (b != 0) {
-        const int64_t t = a % b;
-        a = b;
-        b = t;
-    }
-    const int64_t base = SC / a * kBnThreads;
-    const int64_t items = (int64_t)g->items;
-    int64_t G;
-    if (items == 0)
-        G = kBnThreads;
-    else if (base > items)
-        G = (items + kBnThreads - 1) / kBnThreads * kBnThreads;  // one item per thread
-    else {
-        const int64_t per = (items + kTarget - 1) / kTarget;  // items per thread
-        G = ((items + per - 1) / per + base - 1) / base * base;
-    }
-    g->G = (size_t)G;
-    g->R = SC > 0 ? (int32_t)((G + SC - 1) / SC) : 1;
-    g->NG = (g->R + kBnRowGroup - 1) / kBnRowGroup;
+    bn_plan(*g);
     return MFPSN_OK;
 }
 
@@ -171,6 +135,7 @@ int mfpsn_bn_backward(const mfpsn_desc* desc, const float* x, const float* w, co
         return MFPSN_ERR_ALIGN;
     if (!workspace || workspace_bytes < bn_workspace_bytes(g) || !aligned(workspace, 8))
         return MFPSN_ERR_WORKSPACE;
+    bn_backward_plan(g);
     if (launch_bn_backward(g, x, w, aux, eps, grad_wf, grad_bf, grad_x, grad_w, grad_gamma, grad_beta, workspace,
                            (hipStream_t)stream) != hipSuccess)
         return MFPSN_ERR_HIP;
