@@ -129,8 +129,9 @@ inline int64_t tile_waves(const TileGeom& g, int64_t resident, int64_t slots)
 
 // The plan for one call (es: bytes of a stored element; slots: partial sums
 // the backward's workspace holds, k + 1 values each; < 0: the forward).
-// Returns false when no tile fits.  Whole columns up to 20 KB of LDS per tile,
-// else segments.
+// Returns false when no tile fits: histories above kTileMaxSpan of columns that
+// are too long.  Whole columns up to 20 KB of LDS per tile (columns no longer
+// than their history in any case), else segments.
 //
 // G is chosen by an estimate of the launch's time.  A tile costs R steps (the
 // longest chunk), 0.7 of a step (forward 0.25) per history step of a cut class
@@ -191,6 +192,18 @@ inline bool tile_plan(TileGeom& g, int T, int N, int C, int S, int k, int dilati
         // enough that the history computed twice (backward) is a small share
         if (span > kTileMaxSpan || T < 2)
             return false;
+        if (span >= T) {
+            // a column no longer than its history makes one segment: whole, in
+            // a larger tile (at most 24 T bytes, T <= 1024)
+            g.G = 1;
+            g.Q = 64;
+            g.m = 64 / g.ncls > 0 ? 64 / g.ncls : 1;
+            g.m = g.m < L ? g.m : L;
+            g.by_channel = 1;
+            tile_lds(g, es, os);
+            tile_groups(g, N, slots);
+            return g.lds <= kTileLdsMax && tile_waves(g, 1, slots) > 0;
+        }
         g.d = k == 1 ? 1 : dilation;
         g.ncls = g.d < T ? g.d : T;
         g.G = 1;

@@ -150,15 +150,29 @@ int main()
 EDGES = [(1, 1, 1, 1, 1, 1), (2, 1, 3, 1, 2, 5), (64, 1, 100, 1, 8, 1), (64, 1, 1000, 3, 4, 3), (65, 2, 5, 7, 3, 70),
          (250, 3, 70, 1, 16, 4), (30, 1, 3, 1936, 8, 3), (48, 1, 1000, 3, 2, 3), (1300, 1, 2, 1, 32, 8),
          (2049, 1, 2, 1, 32, 33), (4096, 1, 3, 1, 2, 1024), (5000, 1, 1, 2, 33 - 1, 33), (300, 1, 2, 2, 1, 500),
-         (2100, 1, 1, 2, 3, 512), (1500, 2, 1, 3, 2, 1400), (100, 2, 3, 5, 2, 99)]
+         (2100, 1, 1, 2, 3, 512), (1500, 2, 1, 3, 2, 1400), (100, 2, 3, 5, 2, 99),
+         (900, 2, 3, 1, 2, 1000), (1020, 1, 2, 1, 2, 1024)]
 
 
-@pytest.mark.parametrize("seed", [0, 1, 2])
-def test_every_step_has_one_lane_and_every_access_its_room(tmp_path, seed):
-    src, exe = tmp_path / "drv.cpp", tmp_path / "drv"
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    """Runs the driver over calls (T, N, C, S, k, d, es, backward, resident waves); returns what it found wrong."""
+    path = tmp_path_factory.mktemp("tile_plan")
+    src, exe = path / "drv.cpp", path / "drv"
     src.write_text(DRIVER)
     subprocess.run(["g++", "-std=c++20", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", f"-I{CSRC}",
                     str(src), "-o", str(exe)], check=True, capture_output=True)
+
+    def run(calls):
+        lines = "\n".join(" ".join(map(str, c)) for c in calls)
+        out = subprocess.run([str(exe)], input=lines, capture_output=True, text=True)
+        return "" if out.returncode == 0 else out.stdout or f"exit {out.returncode}"
+
+    return run
+
+
+@pytest.mark.parametrize("seed", [0, 1, 2])
+def test_every_step_has_one_lane_and_every_access_its_room(walk, seed):
     rng = random.Random(seed)
     calls = list(EDGES) if seed == 0 else []
     while len(calls) < 400:
@@ -166,7 +180,13 @@ def test_every_step_has_one_lane_and_every_access_its_room(tmp_path, seed):
         S, C, N = (int(2 ** rng.uniform(0, m)) for m in (7, 6, 3))
         if T * S * C * N <= 300_000:
             calls.append((T, N, C, S, rng.randint(1, 32), int(2 ** rng.uniform(0, rng.choice([3, 11])))))
-    lines = "\n".join(" ".join(map(str, (*c, es, bwd, resident))) for c in calls for es in (2, 4) for bwd in (0, 1)
-                      for resident in (1, 7, 4096))
-    out = subprocess.run([str(exe)], input=lines, capture_output=True, text=True)
-    assert out.returncode == 0, out.stdout
+    assert walk((*c, es, bwd, resident) for c in calls for es in (2, 4) for bwd in (0, 1)
+                for resident in (1, 7, 4096)) == ""
+
+
+def test_histories_about_as_long_as_the_column_have_a_plan(walk):
+    """Every T from 65 to 1100 with dilations at and beyond it, up to the longest history: columns too long for
+    20 KB whole and no longer than their history (order 2: f32 from T = 849, 16-bit from T = 1017)."""
+    assert walk((T, 1, 2, 1, k, d, es, bwd, 7) for T in range(65, 1101) for k in (2, 3)
+                for d in {T - 1, T, T + 1, 1024 // (k - 1) - 1, 1024 // (k - 1)} if d * (k - 1) <= 1024
+                for es in (2, 4) for bwd in (0, 1)) == ""

@@ -7,8 +7,9 @@ bar of the other gradient tests, and exactly for Q8.8.
 
 Shapes: padded rows (whole pieces, half pieces), odd tensors, one column per
 tile with many chunks, rows of several channels cut by a tile, ragged blocks
-of a row, more classes than lanes, dilations past the end, two and three
-segments with a ragged tail, and tensors off 16-byte alignment.
+of a row, more classes than lanes, dilations past the end (in the 20 KB of a
+usual tile and above them), two and three segments with a ragged tail, and
+tensors off 16-byte alignment.
 """
 import pytest
 
@@ -44,6 +45,8 @@ def place(t, offset):
     (4100, 1, 2, 1, 4, 3, 0),     # segments, ragged tail
     (5003, 1, 1, 2, 2, 1000, 0),  # long history between segments, more classes than lanes
     (2, 3, 70, 1, 32, 1, 0),      # two steps, the highest order
+    (900, 2, 3, 1, 2, 1000, 0),   # a dilation past the end of a column too long for 20 KB
+    (1020, 1, 2, 1, 2, 1024, 0),  # the same at the longest history
 ])
 def test_tiles_equal_the_time_first_results(T, N, C, S, k, d, lo, offset, dtype):
     g = torch.Generator().manual_seed(11)
