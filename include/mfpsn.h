@@ -314,9 +314,9 @@ int mfpsn_forward_time_last(const mfpsn_desc* desc, const void* x, const int8_t*
 
 /* Bytes of device workspace mfpsn_backward_time_last needs: 8-byte sums,
  * (k+1)*C of them plus (k+1) per partial-sum slot; the slots are
- * ceil(N*C*S/64) + N*C when T <= 64, else C plus the segment kernel's
- * waves (at most 4 * min(ceil(N*C*S*ceil(T/L)/4), 8192), L as below).
- * Depends on desc only.  Returns a status; *bytes is written on success. */
+ * ceil(N*C*S/64) + N*C when T <= 64, else C plus
+ * 4 * min(ceil(N*C*S*ceil(T/L)/4), 8192), L = 256 (1024 when (k-1)*dilation >
+ * 64).  Depends on desc only.  Returns a status; *bytes is written on success. */
 int mfpsn_backward_time_last_workspace_size(const mfpsn_desc* desc, size_t* bytes);
 
 /* Backward (App. A.3 Eqs. backward_X, backward_W, backward_b, with the taps

@@ -67,11 +67,13 @@ def _units():
     tl_src = os.path.join(CSRC, "mfpsn_tl.hip")
     tl_deps = [tl_src, os.path.join(CSRC, "mfpsn_tl.h"), os.path.join(CSRC, "mfpsn_tl_tile.h"), os.path.join(CSRC, "mfpsn_surrogate.h"),
                os.path.join(INCLUDE, "mfpsn.h")]
-    for tag, flag in (("d0", "-DMFPSN_TL_DTYPE=0"), ("d1", "-DMFPSN_TL_DTYPE=1"), ("d2", "-DMFPSN_TL_DTYPE=2"),
-                      ("dispatch", None)):
-        obj = os.path.join(BUILD, f"tl_{tag}.o")
-        units.append((obj, [HIPCC, *DEVICE_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", *([flag] if flag else []),
-                            "-c", tl_src, "-o", obj], tl_deps))
+    obj = os.path.join(BUILD, "tl_dispatch.o")
+    units.append((obj, [HIPCC, *DEVICE_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", "-c", tl_src, "-o", obj], tl_deps))
+    for dt in DTYPES:
+        for lo, hi in TILE_K_RANGES:
+            obj = os.path.join(BUILD, f"tl_d{dt}_k{lo}-{hi}.o")
+            units.append((obj, [HIPCC, *DEVICE_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", f"-DMFPSN_TL_DTYPE={dt}",
+                                f"-DMFPSN_TL_KLO={lo}", f"-DMFPSN_TL_KHI={hi}", "-c", tl_src, "-o", obj], tl_deps))
     tile_src = os.path.join(CSRC, "mfpsn_tl_tile.hip")
     tile_deps = [tile_src, os.path.join(CSRC, "mfpsn_tl_tile.h"), *tl_deps[1:]]
     obj = os.path.join(BUILD, "tl_tile_dispatch.o")

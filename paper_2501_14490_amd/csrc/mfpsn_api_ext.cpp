@@ -284,14 +284,21 @@ int mfpsn_forward_time_last(const mfpsn_desc* desc, const void* x, const int8_t*
     a.v_th = desc->v_th;
     a.v_th_q = desc->v_th_q;
     fast_range(desc, &a.fast_lo, &a.fast_hi);
-    a.vec_x = aligned(x, 16) ? 1 : 0;
+    a.tdiv = desc->T >= 2 ? (uint32_t)((((uint64_t)1) << 32) / (uint64_t)desc->T + 1) : 0;
     a.vec_s = aligned(spikes, 16) ? 1 : 0;
     a.x_exact = x_exact(desc);
+    const hipStream_t s = (hipStream_t)stream;
+    // (both store H scattered: short columns 82 to 88 us at 2^24 elements, from tiles 44 to 134)
+    if ((h_out && desc->T <= kTlColsMaxT) ||
+        tl_by_columns(false, desc->dtype, M, desc->T, desc->k, desc->dilation)) {
+        a.vec_x = aligned(x, 4 * es) ? 1 : 0;
+        return launch_forward_cols(a, desc->dtype, s) == hipSuccess ? MFPSN_OK : MFPSN_ERR_HIP;
+    }
+    a.vec_x = aligned(x, 16) ? 1 : 0;
     TileGeom g;
     const bool tiles = tile_plan(g, desc->T, desc->N, desc->C, desc->S, desc->k, desc->dilation, es, -1);
     if (tiles && g.Z >= (int64_t)1 << 31)
         return MFPSN_ERR_SHAPE;  // (more elements than any memory holds)
-    const hipStream_t s = (hipStream_t)stream;
     if ((tiles ? launch_forward_tiles(a, g, desc->dtype, s) : launch_forward_time_last(a, desc->dtype, s)) !=
         hipSuccess)
         return MFPSN_ERR_HIP;
@@ -331,7 +338,7 @@ int mfpsn_backward_time_last(const mfpsn_desc* desc, const void* x, const void* 
     const int64_t nseg = ((int64_t)desc->T + seg - 1) / seg;
     if (M >= ((int64_t)1 << 37))
         return MFPSN_ERR_SHAPE;
-    if (desc->T > kTlShortT && (span > kTileMaxSpan || M * nseg >= ((int64_t)1 << 33)))
+    if (desc->T > kTlColsMaxT && (span > kTileMaxSpan || M * nseg >= ((int64_t)1 << 33)))
         return MFPSN_ERR_SHAPE;
     const int64_t total = M * desc->T;
     if (total > 0 && (!x || !grad_spikes || !grad_x))
@@ -375,16 +382,26 @@ int mfpsn_backward_time_last(const mfpsn_desc* desc, const void* x, const void* 
     a.sg = desc->surrogate;
     a.alpha = desc->alpha;
     fast_range(desc, &a.fast_lo, &a.fast_hi);
-    a.vec_x = aligned(x, 16) && aligned(grad_spikes, 16) && aligned(grad_x, 16) ? 1 : 0;
+    a.tdiv = desc->T >= 2 ? (uint32_t)((((uint64_t)1) << 32) / (uint64_t)desc->T + 1) : 0;
     a.x_exact = x_exact(desc);
     a.chunk = 0;
     hipStream_t s = (hipStream_t)stream;
     if (total > 0) {
         const int64_t slots = tl_bwd_slots(M, desc->T, desc->C, desc->N, span);
         TileGeom g;
-        if (!tile_plan(g, desc->T, desc->N, desc->C, desc->S, desc->k, desc->dilation, es, slots) ||
-            g.Z >= (int64_t)1 << 31)
-            return MFPSN_ERR_SHAPE;  // (a plan exists for every accepted call; Z: more elements than any memory holds)
+        bool cols = tl_by_columns(true, desc->dtype, M, desc->T, desc->k, desc->dilation);
+        if (!cols) {
+            if (!tile_plan(g, desc->T, desc->N, desc->C, desc->S, desc->k, desc->dilation, es, slots) ||
+                g.Z >= (int64_t)1 << 31)
+                return MFPSN_ERR_SHAPE;  // (a plan exists for every accepted call; Z: more elements than any memory
+                                         // holds)
+            cols = desc->T <= kTlColsMaxT && tile_short_of_waves(g, desc->k, slots);
+        }
+        if (cols) {
+            a.vec_x = aligned(x, 4 * es) && aligned(grad_spikes, 4 * es) ? 1 : 0;
+            return launch_backward_cols(a, desc->dtype, grad_w, grad_b, s) == hipSuccess ? MFPSN_OK : MFPSN_ERR_HIP;
+        }
+        a.vec_x = aligned(x, 16) && aligned(grad_spikes, 16) && aligned(grad_x, 16) ? 1 : 0;
         if (launch_backward_tiles(a, g, slots, desc->dtype, grad_w, grad_b, s) != hipSuccess)
             return MFPSN_ERR_HIP;
         return MFPSN_OK;

@@ -1,5 +1,6 @@
 // Internal interface of the time-last kernels for the C-ABI layer: the tiles of
-// mfpsn_tl_tile.hip, and the forward for the longest histories (mfpsn_tl.hip).
+// mfpsn_tl_tile.hip, and the kernels of mfpsn_tl.hip: a lane per column for
+// short columns, and the forward for the longest histories.
 // Not installed; not part of the ABI.
 #pragma once
 
@@ -12,9 +13,9 @@ namespace mfpsn {
 
 constexpr int kTlWaves = 4;                 // waves per block
 constexpr int kTlMaxHalo = 2048;            // longest history tl_fwd_kernel stages in LDS
+constexpr int kTlColsMaxT = 64;             // longest column of the lane-per-column kernels
 // What sizes the backward's workspace (tl_bwd_slots)
-constexpr int kTlShortT = 64;               // longest column counted per 64 columns
-constexpr int kTlSeg = 256;                 // steps per counted segment of longer columns
+constexpr int kTlSeg = 256;                 // steps per counted segment of columns above kTlColsMaxT
 constexpr int kTlSegLong = 1024;            // the same for histories (k-1) d above 64
 constexpr int kTlMaxWaves = 32768;          // most waves counted
 
@@ -34,6 +35,7 @@ struct TlArgs {
     float v_th;
     int32_t v_th_q;
     float fast_lo, fast_hi; // range of |x| in which the exponent-add tap is exact
+    uint32_t tdiv;          // columns: floor(2^32 / T) + 1 (T >= 2; 0 when T = 1): e / T = umulhi(e, tdiv) for e < 64 T
     int32_t vec_x;          // x is 16-byte aligned
     int32_t vec_s;          // spikes are 16-byte aligned
     int32_t x_exact;        // every stored input has exact tap products (as Geom::x_exact)
@@ -50,7 +52,7 @@ struct TlBwdArgs {
     const void* bias;       // float[C] or int32[C]
     void* grad_x;           // [N][C][S][T] float, bfloat16 bits or int32
     void* part;             // [slots][k+1] double (float data) or int64 (Q8.8): sums of one wave and
-                            // channel, at tile_slot
+                            // channel, at tile_slot (columns: of one block and (n, c) row, at block + row)
     int64_t M;              // columns, N*C*S
     int32_t T, C, S, k, d;
     int32_t shift_lo, shift_hi;
@@ -59,20 +61,21 @@ struct TlBwdArgs {
     int32_t sg;             // surrogate kind
     float alpha;
     float fast_lo, fast_hi; // range of |x| and |dH| in which the exponent-add tap is exact
+    uint32_t tdiv;          // as TlArgs::tdiv
     int32_t vec_x;          // x, g and grad_x are 16-byte aligned
     int64_t chunk;          // tiles per wave (set by the launcher)
     int32_t x_exact;        // as TlArgs::x_exact
 };
 
 // Slots of partial sums the backward's workspace holds (k + 1 sums each):
-// for columns up to kTlShortT steps one per 64 columns and one per (n, c) row,
+// for columns up to kTlColsMaxT steps one per 64 columns and one per (n, c) row,
 // else one per channel and four per four segments of kTlSeg (kTlSegLong)
 // steps, at most kTlMaxWaves.  The tile plan keeps within them.
 inline int64_t tl_bwd_slots(int64_t M, int32_t T, int32_t C, int32_t N, int64_t span)
 {
     if (M == 0 || T == 0)
         return 0;
-    if (T <= kTlShortT)
+    if (T <= kTlColsMaxT)
         return (M + 63) / 64 + (int64_t)N * C;
     const int seg = span > 64 ? kTlSegLong : kTlSeg;
     const int64_t waves = (M * ((T + seg - 1) / seg) + kTlWaves - 1) / kTlWaves * kTlWaves;
@@ -91,9 +94,55 @@ template <int DT, int KLO> hipError_t tile_forward(const TlArgs& a, const TileGe
 template <int DT, int KLO>
 hipError_t tile_backward(TlBwdArgs& a, const TileGeom& g, int64_t slots, hipStream_t stream);
 
-// One storage type's launchers, each in its own translation unit
-void tl_forward_f32(const TlArgs& a, hipStream_t st);
-void tl_forward_bf16(const TlArgs& a, hipStream_t st);
-void tl_forward_q88(const TlArgs& a, hipStream_t st);
+// Whether a call on columns of T <= kTlColsMaxT steps goes to the
+// lane-per-column kernels.  A tile has at most 64 / d columns and starts anew
+// for each, a column's block takes 64 columns whatever d; against that a tile
+// spreads a column over lanes, so it wins where columns are long, dilations
+// small or lanes scarce, and the column backward loses most of its waves to
+// registers at high orders.  Fitted on MI355X to 9615 calls of both kernels (T
+// 1 to 64, all orders, d 1 to 32, 2^16 to 2^24 elements): the forwards that go
+// to tiles (2089) are 1.34 times faster there on average, the backwards (2416)
+// 1.57 times, and the worst of them 1.16 and 1.09 times slower.  Columns /
+// tiles, us, 2^24 elements, k = 8: bf16 T = 30, d = 1, 3 forward 19, 20 / 20,
+// 27, backward 69, 68 / 63, 77; bf16 T = 64, d = 1 30 / 21 and 93 / 69; f32 T =
+// 32, d = 1 24 / 24 and 90 / 68.
+struct TlColumnsRule {
+    int32_t few_t;      // few columns (at most few_cols): tiles from this length
+    int64_t few_cols;
+    int32_t t0, per_d;  // more: from (t0 + per_d d) / 2 steps
+    int32_t steps;      // and with as many steps per residue class
+    int32_t max_k;      // up to this order
+    int32_t high_k, high_steps;  // from order high_k on: tiles with high_steps steps per class
+    int64_t high_cols;           // of at least so many columns
+};
+constexpr TlColumnsRule kTlColumnsRule[2][3] = {
+    // forward: f32, bf16, Q8.8
+    {{30, 32768, 84, 4, 4, 32, 33, 0, 0}, {32, 49152, 108, 5, 4, 25, 30, 6, 1 << 20}, {28, 32768, 80, 12, 3, 22, 32, 4, 1 << 18}},
+    // backward
+    {{36, 6553, 48, 6, 5, 14, 26, 8, 1 << 17}, {48, 6553, 96, 4, 4, 16, 26, 6, 1 << 17}, {48, 16384, 36, 6, 4, 17, 22, 4, 1 << 18}},
+};
+
+inline bool tl_by_columns(bool backward, int dtype, int64_t M, int32_t T, int32_t k, int32_t d)
+{
+    if (T > kTlColsMaxT)
+        return false;
+    const TlColumnsRule& r = kTlColumnsRule[backward ? 1 : 0][dtype];
+    if (k >= r.high_k && T >= (int64_t)r.high_steps * d && M >= r.high_cols)
+        return false;
+    if (k > r.max_k || T < (int64_t)r.steps * d)
+        return true;
+    return M <= r.few_cols ? T < r.few_t : 2 * T < r.t0 + (int64_t)r.per_d * d;
+}
+
+// The lane-per-column kernels (mfpsn_tl.hip, T <= kTlColsMaxT).  The backward
+// as launch_backward_tiles, with a slot for each block and (n, c) row that share
+// a column.
+hipError_t launch_forward_cols(const TlArgs& a, int dtype, hipStream_t stream);
+hipError_t launch_backward_cols(const TlBwdArgs& a, int dtype, void* grad_w, void* grad_b, hipStream_t stream);
+
+// The same of one storage type for the orders from KLO up to the next of kTileKs
+template <int DT, int KLO> void tl_forward(const TlArgs& a, hipStream_t st);
+template <int DT, int KLO> void tl_cols_forward(const TlArgs& a, hipStream_t st);
+template <int DT, int KLO> void tl_cols_backward(const TlBwdArgs& a, hipStream_t st);
 
 }  // namespace mfpsn

@@ -71,6 +71,12 @@ MFPSN_TILE_FN int64_t tile_slot(const TileGeom& g, int64_t w, int64_t z, int p)
     return (g.by_z ? z * g.Cp : w * g.CH) + cum;
 }
 
+// Waves per CU that the kernels' registers allow
+inline int tile_waves_by_regs(bool backward, int k)
+{
+    return backward ? (k <= 8 ? 16 : k <= 16 ? 12 : 8) : (k <= 8 ? 24 : k <= 16 ? 20 : 12);
+}
+
 // Bytes of one wave's tile: the image of x (es bytes per element, 16-byte
 // pieces as they lie in memory), then the second image (os bytes per
 // element: 4 for dH, 1 for spikes), each with room for the walks' one step
@@ -127,6 +133,15 @@ inline int64_t tile_waves(const TileGeom& g, int64_t resident, int64_t slots)
     return w;
 }
 
+// Whether the slots of partial sums keep a backward plan from the waves that
+// fit (256 CUs; by registers and by LDS)
+inline bool tile_short_of_waves(const TileGeom& g, int k, int64_t slots)
+{
+    const int64_t by_lds = 163840 / ((g.lds + 1279) / 1280 * 1280), by_regs = tile_waves_by_regs(true, k);
+    const int64_t fit = 256 * (by_lds < by_regs ? by_lds : by_regs);
+    return tile_waves(g, fit, slots) < tile_waves(g, fit, -1);
+}
+
 // The plan for one call (es: bytes of a stored element; slots: partial sums
 // the backward's workspace holds, k + 1 values each; < 0: the forward).
 // Returns false when no tile fits: histories above kTileMaxSpan of columns that
@@ -148,7 +163,7 @@ inline bool tile_plan(TileGeom& g, int T, int N, int C, int S, int k, int dilati
     const int os = backward ? 4 : 1;
     const int64_t span = (int64_t)(k - 1) * dilation;
     const double halo = (backward ? 0.7 : 0.25) * (k - 1), fixed = backward ? 1.5 : 6.0;
-    const int by_regs = backward ? (k <= 8 ? 16 : k <= 16 ? 12 : 8) : (k <= 8 ? 24 : k <= 16 ? 20 : 12);  // waves per CU
+    const int by_regs = tile_waves_by_regs(backward, k);
     g.T = T;
     g.C = C;
     g.S = S;

@@ -23,18 +23,16 @@
 // Waves take contiguous runs of tiles that share channels, so taps and
 // grad_w sums stay in registers, and the sums are reduced once per run.
 //
-// Measured on MI355X (forward + backward, us), against the kernels these
-// replace (a lane per column of a transposed tile up to T = 64, a lane per
-// time step of a segment above, which read k values from LDS per step):
+// Measured on MI355X (forward + backward, us), against a lane per
+// column of a transposed tile up to T = 64 and a lane per time step of a segment
+// above, which read k values from LDS per step:
 // f32 [32,128,256,32] k = 8 207 -> 158, f32 [250,256,512] k = 16 d = 2
 // 569 -> 236, Q8.8 [4096,16,1024] k = 32 d = 4 1648 -> 743.  The backward
 // issues 88 to 150 VALU instructions per 64 elements at orders 8 and 16 and
 // keeps the VALUs about 85% busy; LDS bank conflicts are below 2% of the time.
-// Against them bf16 columns of up to about 32 steps lose: a lane takes one
-// class, so a tile has at most 64 / d columns, whose start costs as much as
-// their few steps.  Forward + backward, us: bf16 [30,32,64,44,44] k = 8,
-// d = 1..3 478, 459, 472 -> 504, 487, 585; [16,64,128,16,16] k = 4 148, 148,
-// 153 -> 157, 193, 273.
+// Short columns go to tiles only where they are faster (tl_by_columns): a lane
+// takes one class, so a tile has at most 64 / d columns, whose start costs as
+// much as the few steps of a short one.
 //
 // The arithmetic is that of mfpsn_kernels.hip: a float tap is a fused
 // multiply-add by sign 2^-shift where every value of the tile has exact

@@ -352,7 +352,7 @@ def forward_time_last(desc: MfpsnDesc, x, sign, shift, bias, want_h: bool = Fals
 
 def backward_time_last(desc: MfpsnDesc, x, grad_spikes, sign, shift, bias, workspace=None, stream=None):
     """Backward for x and grad_spikes in the time-last layout [N, C, *spatial,
-    T] (T <= 64): grad_x in the same layout, grad_w [C, k], grad_b [C]."""
+    T]: grad_x in the same layout, grad_w [C, k], grad_b [C]."""
     dev = x.device
     _expect(x, STORAGE[desc.dtype], dev, "x")
     _expect(grad_spikes, STORAGE[desc.dtype], dev, "grad_spikes")

@@ -37,6 +37,8 @@ hipError_t launch_spikes_to_input(const uint8_t*, int64_t, int32_t, void*, hipSt
     return hipSuccess;
 }
 hipError_t launch_forward_time_last(const TlArgs&, int, hipStream_t) { ++stub_launches; return hipSuccess; }
+hipError_t launch_forward_cols(const TlArgs&, int, hipStream_t) { ++stub_launches; return hipSuccess; }
+hipError_t launch_backward_cols(const TlBwdArgs&, int, void*, void*, hipStream_t) { ++stub_launches; return hipSuccess; }
 hipError_t launch_forward_tiles(const TlArgs&, const TileGeom&, int, hipStream_t) { ++stub_launches; return hipSuccess; }
 hipError_t launch_backward_tiles(TlBwdArgs&, const TileGeom&, int64_t, int, void*, void*, hipStream_t)
 {

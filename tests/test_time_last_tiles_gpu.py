@@ -8,8 +8,8 @@ bar of the other gradient tests, and exactly for Q8.8.
 Shapes: padded rows (whole pieces, half pieces), odd tensors, one column per
 tile with many chunks, rows of several channels cut by a tile, ragged blocks
 of a row, more classes than lanes, dilations past the end (in the 20 KB of a
-usual tile and above them), two and three segments with a ragged tail, and
-tensors off 16-byte alignment.
+usual tile and above them), two and three segments with a ragged tail, tensors
+off 16-byte alignment, and the columns that go to a lane each.
 """
 import pytest
 
@@ -47,6 +47,11 @@ def place(t, offset):
     (2, 3, 70, 1, 32, 1, 0),      # two steps, the highest order
     (900, 2, 3, 1, 2, 1000, 0),   # a dilation past the end of a column too long for 20 KB
     (1020, 1, 2, 1, 2, 1024, 0),  # the same at the longest history
+    (30, 2, 64, 9, 8, 3, 0),      # short columns: lane per column, whole blocks of 64
+    (64, 3, 7, 11, 8, 32, 0),     # the longest, a ragged block, rows cut by blocks, a class of two steps
+    (1, 5, 13, 1, 3, 1, 0),       # one step, several channels per block
+    (9, 2, 5, 7, 32, 12, 0),      # a dilation past the end at the highest order
+    (17, 4, 16, 3, 5, 2, -3),     # negative shifts
 ])
 def test_tiles_equal_the_time_first_results(T, N, C, S, k, d, lo, offset, dtype):
     g = torch.Generator().manual_seed(11)
