@@ -37,7 +37,8 @@ DEVICE_FLAGS = [
 HOST_FLAGS = ["-O2", "-std=c++20", "-fPIC", "-Wall", "-Wextra", "-D__HIP_PLATFORM_AMD__",
               "-I/opt/rocm/include"]
 
-K_RANGES = [(1, 8), (9, 12), (13, 16), (17, 20), (21, 23), (24, 26), (27, 29), (30, 31), (32, 32)]
+# (the slowest to compile first, so that none is left over at the end)
+K_RANGES = [(9, 10), (11, 12), (13, 14), (15, 16), (27, 29), (24, 26), (21, 23), (17, 20), (1, 8), (30, 31), (32, 32)]
 TILE_K_RANGES = [(1, 8), (9, 16), (17, 24), (25, 32)]  # kTileKs in mfpsn_tl.h
 DTYPES = [0, 1, 2]  # f32, bf16, q8.8
 

@@ -770,7 +770,15 @@ __device__ __forceinline__ int class_len(const Geom& g, int r) { return g.tq + (
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-template <int K, int DT, int MODE, int NV>
+// VALUES: spikes as values of the storage type (rows as wide as x's), what the
+// next layer reads, else as bytes.  Written here they cost one or three bytes
+// more per element; torch's conversion of the bytes took longer than the whole
+// forward (event vision, bf16, 119 M elements: 257 us beside 221 us with the
+// saved factor; the training step went from 821 to 546 us).  Kernels of their
+// own: chosen by a branch in every step, the byte forward took 1.0 to 1.5 times
+// as long (us, [250,256,512], without / with the branch: f32 k = 4 32 / 37, k =
+// 16 34 / 37; bf16 k = 8 25 / 28; Q8.8 k = 2 27 / 40, k = 32 69 / 72).
+template <int K, int DT, int MODE, int NV, bool VALUES>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void fwd_kernel(FwdArgs a)
 {
     using V = typename IO<DT>::V;
@@ -835,13 +843,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     const uint64_t xrow = (uint64_t)M * es;
     const uint64_t xbytes = (uint64_t)g.T * xrow, sbytes = (uint64_t)g.T * M;
     const int32_t xstep = (int32_t)((uint64_t)d * xrow);
-    // spikes as bytes, or as values of the storage type (rows as wide as x's):
-    // what the next layer reads.  Written here they cost one or three bytes
-    // more per element; torch's conversion of the bytes took longer than the
-    // whole forward (event vision, bf16, 119 M elements: 257 us beside 221 us
-    // with the saved factor; the training step went from 821 to 546 us)
-    const int values = a.spike_es != 1 ? 1 : 0;
-    const int32_t sstep = values ? xstep : (int32_t)((uint64_t)d * M);
+    const int32_t sstep = VALUES ? xstep : (int32_t)((uint64_t)d * M);
     const int want_h = a.h_out != nullptr ? 1 : 0;
     const int want_sg = a.sg_out != nullptr ? 1 : 0;
     // (4-byte rows only when they are written: the planner sizes chunks so
@@ -876,10 +878,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
         const int jb = j0 > 0 ? j0 - (K - 1) : 0;
         const Buf xs = make_buf(a.x, xbytes, ((uint64_t)r + (uint64_t)jb * d) * xrow);
         const uint64_t orow = (uint64_t)r + (uint64_t)j0 * d;
-        const Buf ss = values ? make_buf(a.spikes, xbytes, orow * xrow) : make_buf(a.spikes, sbytes, orow * M);
+        const Buf ss = VALUES ? make_buf(a.spikes, xbytes, orow * xrow) : make_buf(a.spikes, sbytes, orow * M);
         const Buf hs = want_h ? make_buf(a.h_out, sbytes * 4, orow * M * 4) : ss;
         const Buf gs = want_sg ? make_buf(a.sg_out, sbytes * 4, orow * M * 4) : ss;
-        const uint32_t vx = cols.col * es, vs = values ? vx : cols.col, vh = cols.col * 4u;
+        const uint32_t vx = cols.col * es, vs = VALUES ? vx : cols.col, vh = cols.col * 4u;
         const int32_t so_xlast = (Lr - 1 - jb) * xstep;
 
         PV ring[K];  // x[t] at slot t mod k
@@ -967,7 +969,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
                     spk[e / 4] |= (h.v[e] >= vthq ? 1u : 0u) << (8 * (e % 4));
                 }
             }
-            if (values != 0)
+            if constexpr (VALUES)
                 IO<DT>::template store_spikes<NV>(ss, vs, so_s, spk);
             else
                 st_bytes<NV>(ss, vs, so_s, spk);
@@ -1646,19 +1648,19 @@ inline int persistent_blocks(const Geom& g, int resident, bool fill)
     return (int)(blocks > 0 ? blocks : 1);
 }
 
-template <int K, int DT>
-hipError_t fwd_k(FwdArgs& a, hipStream_t st)
+template <int K, int DT, bool VALUES>
+hipError_t fwd_spikes(FwdArgs& a, hipStream_t st)
 {
     static int cache[3][16];
     static int cache_flat[16];
-    void (*kern)(FwdArgs) = fwd_kernel<K, DT, kLaneChannel, 1>;
+    void (*kern)(FwdArgs) = fwd_kernel<K, DT, kLaneChannel, 1, VALUES>;
     int slot = 0;
     if (a.g.mode == kFlat) {
         constexpr int nv = flat_nv(K, DT);
         if constexpr (nv > 0) {
             if (a.g.nv != nv)
                 return hipErrorInvalidValue;
-            kern = fwd_kernel<K, DT, kFlat, nv>;
+            kern = fwd_kernel<K, DT, kFlat, nv, VALUES>;
             a.g.blocks = persistent_blocks(a.g, resident_blocks(kern, cache_flat), false);
             hipLaunchKernelGGL(kern, dim3(a.g.blocks, a.g.groups), dim3(kThreads), 0, st, a);
             return hipGetLastError();
@@ -1669,19 +1671,25 @@ hipError_t fwd_k(FwdArgs& a, hipStream_t st)
     if (a.g.mode == kPlane) {
         if (a.g.nv == 2) {
             if constexpr (K <= kPairMaxK) {
-                kern = fwd_kernel<K, DT, kPlane, 2>;
+                kern = fwd_kernel<K, DT, kPlane, 2, VALUES>;
                 slot = 2;
             } else {
                 return hipErrorInvalidValue;
             }
         } else {
-            kern = fwd_kernel<K, DT, kPlane, 1>;
+            kern = fwd_kernel<K, DT, kPlane, 1, VALUES>;
             slot = 1;
         }
     }
     a.g.blocks = persistent_blocks(a.g, resident_blocks(kern, cache[slot]), false);
     hipLaunchKernelGGL(kern, dim3(a.g.blocks, a.g.groups), dim3(kThreads), 0, st, a);
     return hipGetLastError();
+}
+
+template <int K, int DT>
+hipError_t fwd_k(FwdArgs& a, hipStream_t st)
+{
+    return a.spike_es != 1 ? fwd_spikes<K, DT, true>(a, st) : fwd_spikes<K, DT, false>(a, st);
 }
 
 template <int K, int DT, int HS>
