@@ -88,14 +88,18 @@ inline double bn_backward_cost(const BnGeom& g)
 // two waves per SIMD are resident and the shared plan's three leave a second
 // round that is mostly empty.  There the fewest threads of shortest estimated
 // time are taken among the numbers of chunks, never more threads than the
-// shared plan has: the workspace is sized by it.  Lower orders hold three
-// waves or more; above 22 the walk spills and one is resident, unmeasured.
+// shared plan has: the workspace is sized by it.  It is taken where the estimate
+// falls to 0.77 of the shared plan's: of 162 layers (11 shapes, orders 15 to 22,
+// d = 1 to 3) the 78 with 0.42 to 0.75 took 0.72 to 1.00 of its time, 0.91 on
+// average, and those at 0.79 and 0.80 ([128,64,100,13] d = 2) 1.05 and 1.00.
+// Lower orders hold three waves or more; above 22 the walk spills and one is
+// resident, unmeasured.
 inline void bn_backward_plan(BnGeom& g)
 {
     if (g.k < 15 || g.k > 22 || g.items == 0)
         return;
     BnGeom best = g;
-    double least = 0.8 * bn_backward_cost(g);
+    double least = 0.77 * bn_backward_cost(g);
     const int64_t L = ((int64_t)g.T + g.d - 1) / g.d;
     for (int64_t nch = 1; nch == 1 || (nch <= 64 && nch * 2 * g.k <= L); ++nch)
         for (int rounds = 1; rounds <= 2; ++rounds) {

@@ -54,3 +54,32 @@ def test_backward_plan(tmp_path):
                     f"-I{os.path.join(ROOT, 'include')}", str(src), "-o", str(exe)], check=True)
     p = subprocess.run([str(exe)], capture_output=True, text=True)
     assert p.returncode == 0, p.stdout
+
+
+SLOWER = r"""
+#include "mfpsn_bn.h"
+using namespace mfpsn;
+int main()
+{
+    for (int k : {15, 16}) {
+        BnGeom g{};
+        g.T = 128; g.N = 64; g.C = 100; g.S = 13; g.k = k; g.d = 2;
+        g.M = (size_t)g.N * g.C * g.S;
+        bn_plan(g);
+        BnGeom b = g;
+        bn_backward_plan(b);
+        if (b.G != g.G || b.nch != g.nch)
+            return 1;
+    }
+    return 0;
+}
+"""
+
+
+def test_a_plan_hardly_better_by_its_estimate_is_not_taken(tmp_path):
+    """[128,64,100,13] d = 2: half the waves, one chunk instead of two; 70.4 us instead of 67.3 at order 16."""
+    src, exe = tmp_path / "slower.cpp", tmp_path / "slower"
+    src.write_text(SLOWER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", f"-I{CSRC}",
+                    f"-I{os.path.join(ROOT, 'include')}", str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)]).returncode == 0
