@@ -286,17 +286,16 @@ int mfpsn_forward_time_last(const mfpsn_desc* desc, const void* x, const int8_t*
     fast_range(desc, &a.fast_lo, &a.fast_hi);
     a.tdiv = desc->T >= 2 ? (uint32_t)((((uint64_t)1) << 32) / (uint64_t)desc->T + 1) : 0;
     a.vec_s = aligned(spikes, 16) ? 1 : 0;
+    a.vec_h = aligned(h_out, 16) && aligned(spikes, 4) ? 1 : 0;
     a.x_exact = x_exact(desc);
     const hipStream_t s = (hipStream_t)stream;
-    // (both store H scattered: short columns 82 to 88 us at 2^24 elements, from tiles 44 to 134)
-    if ((h_out && desc->T <= kTlColsMaxT) ||
-        tl_by_columns(false, desc->dtype, M, desc->T, desc->k, desc->dilation)) {
+    if (tl_by_columns(false, desc->dtype, M, desc->T, desc->k, desc->dilation)) {
         a.vec_x = aligned(x, 4 * es) ? 1 : 0;
         return launch_forward_cols(a, desc->dtype, s) == hipSuccess ? MFPSN_OK : MFPSN_ERR_HIP;
     }
     a.vec_x = aligned(x, 16) ? 1 : 0;
     TileGeom g;
-    const bool tiles = tile_plan(g, desc->T, desc->N, desc->C, desc->S, desc->k, desc->dilation, es, -1);
+    const bool tiles = tile_plan(g, desc->T, desc->N, desc->C, desc->S, desc->k, desc->dilation, es, -1, h_out != nullptr);
     if (tiles && g.Z >= (int64_t)1 << 31)
         return MFPSN_ERR_SHAPE;  // (more elements than any memory holds)
     if ((tiles ? launch_forward_tiles(a, g, desc->dtype, s) : launch_forward_time_last(a, desc->dtype, s)) !=

@@ -38,6 +38,7 @@ struct TlArgs {
     uint32_t tdiv;          // columns: floor(2^32 / T) + 1 (T >= 2; 0 when T = 1): e / T = umulhi(e, tdiv) for e < 64 T
     int32_t vec_x;          // x is 16-byte aligned
     int32_t vec_s;          // spikes are 16-byte aligned
+    int32_t vec_h;          // h_out is 16-byte, spikes are 4-byte aligned
     int32_t x_exact;        // every stored input has exact tap products (as Geom::x_exact)
 };
 

@@ -79,14 +79,14 @@ inline int tile_waves_by_regs(bool backward, int k)
 
 // Bytes of one wave's tile: the image of x (es bytes per element, 16-byte
 // pieces as they lie in memory), then the second image (os bytes per
-// element: 4 for dH, 1 for spikes), each with room for the walks' one step
-// of read-ahead on either side.
-inline void tile_lds(TileGeom& g, int es, int os)
+// element: 4 for dH or H, 1 for spikes), each with room for the walks' one
+// step of read-ahead on either side.
+inline void tile_lds(TileGeom& g, int es, int os, bool backward)
 {
     g.xs = g.T + (g.G > 1 && (int64_t)g.T * es % 16 == 0 ? 4 / es : 0);
     g.os = g.T + (g.G > 1 && (int64_t)g.T * os % 16 == 0 ? 4 / os : 0);
     g.tdiv = g.T > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint64_t)g.T + 1) : 0;
-    const int64_t ahead = os == 4 ? g.span : 0;  // steps after a segment the backward needs
+    const int64_t ahead = backward ? g.span : 0;  // steps after a segment the backward needs
     const int64_t xn = g.nseg == 1 ? (int64_t)g.G * g.xs : (int64_t)g.seg + g.span + ahead;
     const int64_t on = g.nseg == 1 ? (int64_t)g.G * g.os : g.seg + ahead;
     const int64_t v = 16 / es;
@@ -143,7 +143,8 @@ inline bool tile_short_of_waves(const TileGeom& g, int k, int64_t slots)
 }
 
 // The plan for one call (es: bytes of a stored element; slots: partial sums
-// the backward's workspace holds, k + 1 values each; < 0: the forward).
+// the backward's workspace holds, k + 1 values each; < 0: the forward, with its
+// potentials kept if want_h).
 // Returns false when no tile fits: histories above kTileMaxSpan of columns that
 // are too long.  Whole columns up to 20 KB of LDS per tile (columns no longer
 // than their history in any case), else segments.
@@ -157,10 +158,11 @@ inline bool tile_short_of_waves(const TileGeom& g, int k, int64_t slots)
 // per SIMD that the registers allow the time grows as their inverse.  One
 // wave alone on a SIMD takes about twice its instructions' issue time, and
 // 1024 SIMDs share the tiles: few columns take the G that spreads them.
-inline bool tile_plan(TileGeom& g, int T, int N, int C, int S, int k, int dilation, int es, int64_t slots)
+inline bool tile_plan(TileGeom& g, int T, int N, int C, int S, int k, int dilation, int es, int64_t slots,
+                      bool want_h = false)
 {
     const bool backward = slots >= 0;
-    const int os = backward ? 4 : 1;
+    const int os = backward || want_h ? 4 : 1;
     const int64_t span = (int64_t)(k - 1) * dilation;
     const double halo = (backward ? 0.7 : 0.25) * (k - 1), fixed = backward ? 1.5 : 6.0;
     const int by_regs = tile_waves_by_regs(backward, k);
@@ -183,7 +185,7 @@ inline bool tile_plan(TileGeom& g, int T, int N, int C, int S, int k, int dilati
         t.m = t.Q / t.ncls > 0 ? t.Q / t.ncls : 1;
         t.m = t.m < L ? t.m : L;
         t.by_channel = G <= S;
-        tile_lds(t, es, os);
+        tile_lds(t, es, os, backward);
         if (t.lds > 20480 || (!t.by_channel && G > (int64_t)S * C))
             break;
         tile_groups(t, N, slots);
@@ -215,7 +217,7 @@ inline bool tile_plan(TileGeom& g, int T, int N, int C, int S, int k, int dilati
             g.m = 64 / g.ncls > 0 ? 64 / g.ncls : 1;
             g.m = g.m < L ? g.m : L;
             g.by_channel = 1;
-            tile_lds(g, es, os);
+            tile_lds(g, es, os, backward);
             tile_groups(g, N, slots);
             return g.lds <= kTileLdsMax && tile_waves(g, 1, slots) > 0;
         }
@@ -233,7 +235,7 @@ inline bool tile_plan(TileGeom& g, int T, int N, int C, int S, int k, int dilati
         if (g.seg < span)
             g.seg = (int32_t)span;
         g.nseg = (T + g.seg - 1) / g.seg;
-        tile_lds(g, es, os);
+        tile_lds(g, es, os, backward);
         tile_groups(g, N, slots);
         if (g.nseg == 1 || g.lds > kTileLdsMax || tile_waves(g, 1, slots) < 1)
             return false;

@@ -348,6 +348,42 @@ __device__ __forceinline__ void unstage(const TileGeom& g, const I* img, int off
         base[off + t0 + lane] = value(t0 + lane);
 }
 
+// As unstage, for an image of potentials: stores them to h and the spikes they
+// are to spikes, four at once (rows of padded images are whole groups of four).
+template <typename V>
+__device__ __forceinline__ void unstage_h(const TileGeom& g, const V* img, int off, int count, V v_th, V* h,
+                                          uint8_t* spikes, int64_t d0, bool vec)
+{
+    const int lane = (int)threadIdx.x;
+    const bool padded = g.os != g.T;
+    auto one = [&](int e) __attribute__((always_inline)) {
+        const V v = img[off + e + row_shift(g, e, g.os)];
+        h[d0 + e] = v;
+        spikes[d0 + e] = v >= v_th ? 1 : 0;
+    };
+    if (!vec) {
+        for (int i = lane; i < count; i += 64)
+            one(i);
+        return;
+    }
+    const int q0 = (off + 3) / 4, q1 = (off + count) / 4;  // whole groups
+    for (int q = q0 + lane; q < q1; q += 64) {
+        const V4 w = get4((const char*)(img + 4 * q + (padded ? row_shift(g, 4 * q - off, g.os) : 0)), padded);
+        uint32_t s = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            s |= (__builtin_bit_cast(V, (uint32_t)w[j]) >= v_th ? 1u : 0u) << (8 * j);
+        __builtin_nontemporal_store(w, (V4*)(h + (d0 - off)) + q);
+        __builtin_nontemporal_store(s, (uint32_t*)(spikes + (d0 - off)) + q);
+    }
+    const int head = min(q0 * 4 - off, count);
+    if (lane < head)
+        one(lane);
+    const int t0 = q1 * 4 - off, tail = count - t0;  // (no whole group, and t0 below 0: the head has it all)
+    if (q1 >= q0 && lane < tail)
+        one(t0 + lane);
+}
+
 // The tiles of a wave in turn: columns col0 .. col0 + rows - 1 of group p,
 // steps from t0 (all wave-uniform; the divisions are done once)
 struct Cursor {
@@ -424,7 +460,12 @@ template <int K, typename Step> __device__ __forceinline__ void walk_steps(int t
     }
 }
 
-template <int DT, int K>
+// WANT_H: the second image holds H (4 bytes per element), from which H and the
+// spikes are stored as they lie in memory, else the spikes.  Stored by the lanes
+// as they walk, 64 scattered values per step, H took 131 us for f32
+// [512,16,64,32] k = 4 d = 1 and 85 us for T = 1000 k = 8 d = 1 (2^24 elements);
+// from the image 47 and 44 (two passes over the image beside the 4 bytes more).
+template <int DT, int K, bool WANT_H>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 : 3))) void tile_fwd_kernel(
     TlArgs a, TileGeom g, int64_t chunk)
 {
@@ -432,10 +473,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 
     using V = typename IO::V;
     using E = typename IO::E;
     constexpr bool kF = DT != MFPSN_Q8_8;
-    constexpr int es = (int)sizeof(E);
+    constexpr int es = (int)sizeof(E), os = WANT_H ? 4 : 1;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char* xi = lds;
-    uint8_t* si = (uint8_t*)(lds + g.lds_x);
+    char* oi = lds + g.lds_x;
     const int xstep = g.d * es;
     const int lane = (int)threadIdx.x;
     const int row = min(lane / g.Q, g.G - 1), q = lane - row * g.Q;
@@ -446,7 +487,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 
     if (t >= tend)
         return;
     TileTaps<DT, K> taps;
-    V bias = V(0);
+    V bias = V(0), v_th;
+    if constexpr (kF)
+        v_th = a.v_th;
+    else
+        v_th = a.v_th_q;
     int cur = -1, cur_W = -1, top = 0;
     const int ch = q / g.ncls, r0 = q - ch * g.ncls;  // (ch 0 when a row has more classes than lanes)
     const int N = (int)(a.M / ((int64_t)g.S * g.C));
@@ -486,14 +531,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 
         if constexpr (kF)
             slow = check && (a.fast_hi < INFINITY || __builtin_amdgcn_ballot_w64(chk.inexact(a.fast_lo)) != 0);
         wave_sync();
-        const int soff = a.vec_s ? (int)(e0 & 15) : 0;
+        const int ooff = WANT_H ? (a.vec_h ? (int)(e0 & 3) : 0) : a.vec_s ? (int)(e0 & 15) : 0;
         // byte addresses of the row's first step in the images
-        const int xrow = (off + before + row * g.xs) * es, srow = g.lds_x + soff + row * g.os;
+        const int xrow = (off + before + row * g.xs) * es, orow = g.lds_x + (ooff + row * g.os) * os;
         auto walk = [&](auto exact, const Part& pt) __attribute__((always_inline)) {
             constexpr bool EX = decltype(exact)::value;
             const int hist = tl.t0 > 0 ? K : pt.j0;  // steps of the class before the chunk (at least k, or all)
             const int at = pt.r + pt.j0 * g.d;
-            int xa = xrow + at * es, sa = srow + at;
+            int xa = xrow + at * es, oa = orow + at * os;
             V ring[K];  // step s of the chunk at slot s mod k
 #pragma unroll
             for (int b = 0; b < K; ++b)
@@ -505,7 +550,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 
                     ring[K - b] = b <= hist ? v : V(0);
                 }
             }
-            float* hrow = a.h_out != nullptr ? (float*)a.h_out + e0 + (int64_t)row * g.T : nullptr;
             walk_steps<K>(top, pt.j1 - pt.j0, [&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
                 ring[u] = IO::get(*(const E*)(lds + xa));
@@ -522,16 +566,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 
                         acc = taps.template add<EX>(acc, ring[(u + 1 + i) % K], i);
                 }
                 const V h = acc + bias;
-                bool fire;
-                if constexpr (kF)
-                    fire = h >= a.v_th;
+                if constexpr (WANT_H)
+                    *(V*)(lds + oa) = h;
                 else
-                    fire = h >= a.v_th_q;
-                lds[sa] = fire ? 1 : 0;
-                if (hrow != nullptr)
-                    hrow[sa - srow] = __builtin_bit_cast(float, h);
+                    lds[oa] = h >= v_th ? 1 : 0;
                 xa += xstep;
-                sa += g.d;
+                oa += g.d * os;
             });
         };
         if (mine && row < tl.rows) {
@@ -547,7 +587,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 
             }
         }
         wave_sync();
-        unstage<uint8_t, uint8_t>(g, si, soff, g.nseg == 1 ? count : W, g.os, a.spikes, e0, a.vec_s);
+        const int out = g.nseg == 1 ? count : W;
+        if constexpr (WANT_H)
+            unstage_h<V>(g, (const V*)oi, ooff, out, v_th, (V*)a.h_out, a.spikes, e0, a.vec_h);
+        else
+            unstage<uint8_t, uint8_t>(g, (const uint8_t*)oi, ooff, out, g.os, a.spikes, e0, a.vec_s);
         wave_sync();  // every read of the images before the next tile's writes
     }
 }
@@ -916,10 +960,10 @@ template <typename Kern> int64_t resident_waves(Kern kern, int (&cache)[2][16], 
     return (int64_t)per * cache[1][s];
 }
 
-template <int DT, int K> hipError_t fwd_tiles(const TlArgs& a, const TileGeom& g, hipStream_t st)
+template <int DT, int K, bool WANT_H> hipError_t fwd_tiles(const TlArgs& a, const TileGeom& g, hipStream_t st)
 {
     static int cache[2][16];
-    auto kern = tile_fwd_kernel<DT, K>;
+    auto kern = tile_fwd_kernel<DT, K, WANT_H>;
     const int64_t waves = tile_waves(g, resident_waves(kern, cache, g.lds), -1);
     const int64_t chunk = (g.tiles + waves - 1) / waves;
     const unsigned blocks = (unsigned)((g.tiles + chunk - 1) / chunk);
@@ -944,7 +988,10 @@ template <int DT, int LO, int... Ks>
 hipError_t fwd_range(const TlArgs& a, const TileGeom& g, hipStream_t st, std::integer_sequence<int, Ks...>)
 {
     hipError_t e = hipErrorInvalidValue;
-    (void)((a.k == LO + Ks ? (e = fwd_tiles<DT, LO + Ks>(a, g, st), true) : false) || ...);
+    if (a.h_out != nullptr)
+        (void)((a.k == LO + Ks ? (e = fwd_tiles<DT, LO + Ks, true>(a, g, st), true) : false) || ...);
+    else
+        (void)((a.k == LO + Ks ? (e = fwd_tiles<DT, LO + Ks, false>(a, g, st), true) : false) || ...);
     return e;
 }
 template <int DT, int LO, int... Ks>

@@ -28,12 +28,14 @@ DRIVER = r"""
 #include "mfpsn_tl.h"
 using namespace mfpsn;
 #define CHECK(x) do { if (!(x)) { printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
-int one(int T, int N, int C, int S, int k, int d, int es, bool bwd, long resident)
+// bwd 0: forward, 1: backward, 2: forward that keeps H
+int one(int T, int N, int C, int S, int k, int d, int es, int kind, long resident)
 {
+    const bool bwd = kind == 1;
     const long M = (long)N * C * S, span = (long)(k - 1) * d;
     const long slots = bwd ? tl_bwd_slots(M, T, C, N, span) : -1;
     TileGeom g;
-    if (!tile_plan(g, T, N, C, S, k, d, es, slots)) {
+    if (!tile_plan(g, T, N, C, S, k, d, es, slots, kind == 2)) {
         CHECK(T > 64 && span > kTileMaxSpan);  // what the entry points refuse, or run untiled
         return 0;
     }
@@ -41,7 +43,7 @@ int one(int T, int N, int C, int S, int k, int d, int es, bool bwd, long residen
     const long waves = tile_waves(g, resident, slots);
     CHECK(waves >= 1);
     const long chunk = (g.tiles + waves - 1) / waves;
-    const int os = bwd ? 4 : 1, v = 16 / es;
+    const int os = kind > 0 ? 4 : 1, v = 16 / es;
     std::vector<unsigned char> seen(M * T, 0);
     std::set<long> used;
     for (long w = 0; w * chunk < g.tiles; ++w) {
@@ -91,7 +93,7 @@ int one(int T, int N, int C, int S, int k, int d, int es, bool bwd, long residen
                 CHECK(g.lds_x + ((off + count + v - 1) / v * v + (rows - 1) * (g.os - T)) * os <= g.lds);
             }
             if (!bwd)
-                CHECK(g.lds_x + 16 + count + (rows - 1) * (g.os - T) <= g.lds);
+                CHECK(g.lds_x + (16 + count + (rows - 1) * (g.os - T)) * os <= g.lds);
             for (int lane = 0; lane < 64; ++lane) {
                 const int row = std::min(lane / g.Q, g.G - 1), q = lane - row * g.Q;
                 if (!(q < g.ncls * g.m && lane < g.G * g.Q) || row >= rows)
@@ -156,7 +158,8 @@ EDGES = [(1, 1, 1, 1, 1, 1), (2, 1, 3, 1, 2, 5), (64, 1, 100, 1, 8, 1), (64, 1, 
 
 @pytest.fixture(scope="module")
 def walk(tmp_path_factory):
-    """Runs the driver over calls (T, N, C, S, k, d, es, backward, resident waves); returns what it found wrong."""
+    """Runs the driver over calls (T, N, C, S, k, d, es, 0 forward / 1 backward / 2 forward that
+    keeps H, resident waves); returns what it found wrong."""
     path = tmp_path_factory.mktemp("tile_plan")
     src, exe = path / "drv.cpp", path / "drv"
     src.write_text(DRIVER)
@@ -180,7 +183,7 @@ def test_every_step_has_one_lane_and_every_access_its_room(walk, seed):
         S, C, N = (int(2 ** rng.uniform(0, m)) for m in (7, 6, 3))
         if T * S * C * N <= 300_000:
             calls.append((T, N, C, S, rng.randint(1, 32), int(2 ** rng.uniform(0, rng.choice([3, 11])))))
-    assert walk((*c, es, bwd, resident) for c in calls for es in (2, 4) for bwd in (0, 1)
+    assert walk((*c, es, bwd, resident) for c in calls for es in (2, 4) for bwd in (0, 1, 2)
                 for resident in (1, 7, 4096)) == ""
 
 

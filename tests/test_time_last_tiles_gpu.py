@@ -9,7 +9,7 @@ Shapes: padded rows (whole pieces, half pieces), odd tensors, one column per
 tile with many chunks, rows of several channels cut by a tile, ragged blocks
 of a row, more classes than lanes, dilations past the end (in the 20 KB of a
 usual tile and above them), two and three segments with a ragged tail, tensors
-off 16-byte alignment, and the columns that go to a lane each.
+1, 2 and 4 elements off 16-byte alignment, and the columns that go to a lane each.
 """
 import pytest
 
@@ -33,7 +33,7 @@ def place(t, offset):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "q8_8"])
-@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("offset", [0, 1, 2, 4])
 @pytest.mark.parametrize("T,N,C,S,k,d,lo", [
     (48, 3, 5, 9, 4, 1, 0),       # padded rows, ragged blocks of a row
     (20, 5, 7, 3, 3, 2, 0),       # half pieces (16-bit), channels cut by tiles
@@ -75,6 +75,8 @@ def test_tiles_equal_the_time_first_results(T, N, C, S, k, d, lo, offset, dtype)
     spikes_l, h_l = (torch.empty(spikes.numel() + offset, dtype=t, device=DEV)[offset:].view(xl.shape)
                      for t in (torch.uint8, h.dtype))
     mfpsn.mfpsn_forward_time_last(desc, xl, sign, shift, bias, spikes_l, h_l)
+    spikes_n = torch.empty(spikes.numel() + offset, dtype=torch.uint8, device=DEV)[offset:].view(xl.shape)
+    mfpsn.mfpsn_forward_time_last(desc, xl, sign, shift, bias, spikes_n)  # (kernels of their own)
     gx_l, gw_l, gb_l = mfpsn.backward_time_last(desc, xl, gl, sign, shift, bias)
 
     def same(a, b):
@@ -82,7 +84,7 @@ def test_tiles_equal_the_time_first_results(T, N, C, S, k, d, lo, offset, dtype)
         bits = {2: torch.int16, 4: torch.int32}.get(b.element_size(), b.dtype)
         return torch.equal(a.contiguous().view(bits), b.view(bits))
 
-    assert same(spikes_l, spikes)
+    assert same(spikes_l, spikes) and same(spikes_n, spikes)
     assert same(h_l, h)
     assert same(gx_l, gx)
     for got, want in ((gw_l, gw), (gb_l, gb)):
