@@ -293,7 +293,7 @@ int mfpsn_forward_time_last(const mfpsn_desc* desc, const void* x, const int8_t*
         a.vec_x = aligned(x, 4 * es) ? 1 : 0;
         return launch_forward_cols(a, desc->dtype, s) == hipSuccess ? MFPSN_OK : MFPSN_ERR_HIP;
     }
-    a.vec_x = aligned(x, 16) ? 1 : 0;
+    a.vec_x = aligned(x, 4) ? 1 : 0;
     TileGeom g;
     const bool tiles = tile_plan(g, desc->T, desc->N, desc->C, desc->S, desc->k, desc->dilation, es, -1, h_out != nullptr);
     if (tiles && g.Z >= (int64_t)1 << 31)
@@ -400,7 +400,8 @@ int mfpsn_backward_time_last(const mfpsn_desc* desc, const void* x, const void* 
             a.vec_x = aligned(x, 4 * es) && aligned(grad_spikes, 4 * es) ? 1 : 0;
             return launch_backward_cols(a, desc->dtype, grad_w, grad_b, s) == hipSuccess ? MFPSN_OK : MFPSN_ERR_HIP;
         }
-        a.vec_x = aligned(x, 16) && aligned(grad_spikes, 16) && aligned(grad_x, 16) ? 1 : 0;
+        a.vec_x = aligned(x, 4) && aligned(grad_spikes, 4) ? 1 : 0;
+        a.vec_o = aligned(grad_x, desc->dtype == MFPSN_BF16 ? 8 : 16) ? 1 : 0;
         if (launch_backward_tiles(a, g, slots, desc->dtype, grad_w, grad_b, s) != hipSuccess)
             return MFPSN_ERR_HIP;
         return MFPSN_OK;

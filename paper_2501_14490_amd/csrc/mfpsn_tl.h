@@ -36,7 +36,7 @@ struct TlArgs {
     int32_t v_th_q;
     float fast_lo, fast_hi; // range of |x| in which the exponent-add tap is exact
     uint32_t tdiv;          // columns: floor(2^32 / T) + 1 (T >= 2; 0 when T = 1): e / T = umulhi(e, tdiv) for e < 64 T
-    int32_t vec_x;          // x is 16-byte aligned
+    int32_t vec_x;          // x is 4-byte aligned (columns: to 4 elements)
     int32_t vec_s;          // spikes are 16-byte aligned
     int32_t vec_h;          // h_out is 16-byte, spikes are 4-byte aligned
     int32_t x_exact;        // every stored input has exact tap products (as Geom::x_exact)
@@ -63,7 +63,8 @@ struct TlBwdArgs {
     float alpha;
     float fast_lo, fast_hi; // range of |x| and |dH| in which the exponent-add tap is exact
     uint32_t tdiv;          // as TlArgs::tdiv
-    int32_t vec_x;          // x, g and grad_x are 16-byte aligned
+    int32_t vec_x;          // x and g are 4-byte aligned (columns: to 4 elements)
+    int32_t vec_o;          // tiles: grad_x is 16-byte aligned (bf16: 8-byte)
     int64_t chunk;          // tiles per wave (set by the launcher)
     int32_t x_exact;        // as TlArgs::x_exact
 };

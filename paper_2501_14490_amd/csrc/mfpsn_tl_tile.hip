@@ -189,8 +189,8 @@ __device__ __forceinline__ V4 get4(const char* p, bool padded)
 // its element e0 mod kV, so that 16-byte pieces stay 16-byte pieces) and,
 // with PAIR, `count2` from f0 of src2 into img2, widened to 32 bits; the loads
 // of up to U pieces of each are issued before the first LDS write.  off and
-// off2 get the offsets of the first elements.  Tensors off 16-byte alignment
-// (vec = 0) go element by element.  With CHECK, the values of src go to chk.
+// off2 get the offsets of the first elements.  The 16-byte buffer loads need
+// 4-byte alignment; 16-bit tensors off it (vec = 0) go element by element.  With CHECK, the values of src go to chk.
 template <int DT, bool PAIR, bool CHECK, int U>
 __device__ __forceinline__ void stage(const TileGeom& g, const void* src, int64_t e0, int count, const void* src2,
                                       int64_t f0, int count2, int64_t total, bool vec, char* img, char* img2,
@@ -872,9 +872,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 8 ? 4 :
         wave_sync();
         const int out = whole ? count : own;
         if constexpr (DT == MFPSN_BF16)
-            unstage<float, uint16_t>(g, (const float*)di, doff, out, g.os, (uint16_t*)a.grad_x, e0, a.vec_x);
+            unstage<float, uint16_t>(g, (const float*)di, doff, out, g.os, (uint16_t*)a.grad_x, e0, a.vec_o);
         else
-            unstage<V, V>(g, (const V*)di, doff, out, g.os, (V*)a.grad_x, e0, a.vec_x);
+            unstage<V, V>(g, (const V*)di, doff, out, g.os, (V*)a.grad_x, e0, a.vec_o);
         wave_sync();  // every read of the images before the next tile's writes
     }
     flush();
