@@ -103,8 +103,8 @@ hipError_t tile_backward(TlBwdArgs& a, const TileGeom& g, int64_t slots, hipStre
 // small or lanes scarce, and the column backward loses most of its waves to
 // registers at high orders.  Fitted on MI355X to 9615 calls of both kernels (T
 // 1 to 64, all orders, d 1 to 32, 2^16 to 2^24 elements): the forwards that go
-// to tiles (2089) are 1.34 times faster there on average, the backwards (2416)
-// 1.57 times, and the worst of them 1.16 and 1.09 times slower.  Columns /
+// to tiles (2089) are 1.34 times faster there on average, the backwards (2881)
+// 1.54 times, and the worst of them 1.16 and 1.09 times slower.  Columns /
 // tiles, us, 2^24 elements, k = 8: bf16 T = 30, d = 1, 3 forward 19, 20 / 20,
 // 27, backward 69, 68 / 63, 77; bf16 T = 64, d = 1 30 / 21 and 93 / 69; f32 T =
 // 32, d = 1 24 / 24 and 90 / 68.
@@ -114,14 +114,23 @@ struct TlColumnsRule {
     int32_t t0, per_d;  // more: from (t0 + per_d d) / 2 steps
     int32_t steps;      // and with as many steps per residue class
     int32_t max_k;      // up to this order
-    int32_t high_k, high_steps;  // from order high_k on: tiles with high_steps steps per class
-    int64_t high_cols;           // of at least so many columns
+    // of many columns (at least cols) also those of order k and more from t
+    // steps, with as many as `steps` per class
+    struct {
+        int64_t cols;
+        int32_t k, t, steps;
+    } many[2];
 };
+constexpr int64_t kTlNone = INT64_MAX;  // no number of columns
 constexpr TlColumnsRule kTlColumnsRule[2][3] = {
     // forward: f32, bf16, Q8.8
-    {{30, 32768, 84, 4, 4, 32, 33, 0, 0}, {32, 49152, 108, 5, 4, 25, 30, 6, 1 << 20}, {28, 32768, 80, 12, 3, 22, 32, 4, 1 << 18}},
+    {{30, 32768, 84, 4, 4, 32, {{kTlNone, 1, 1, 1}, {kTlNone, 1, 1, 1}}},
+     {32, 49152, 108, 5, 4, 25, {{1 << 20, 30, 1, 6}, {kTlNone, 1, 1, 1}}},
+     {28, 32768, 80, 12, 3, 22, {{1 << 18, 32, 1, 4}, {kTlNone, 1, 1, 1}}}},
     // backward
-    {{36, 6553, 48, 6, 5, 14, 26, 8, 1 << 17}, {48, 6553, 96, 4, 4, 16, 26, 6, 1 << 17}, {48, 16384, 36, 6, 4, 17, 22, 4, 1 << 18}},
+    {{36, 6553, 48, 6, 5, 14, {{1 << 17, 26, 1, 8}, {1 << 17, 9, 40, 8}}},
+     {48, 6553, 96, 4, 4, 16, {{1 << 17, 26, 1, 6}, {kTlNone, 1, 1, 1}}},
+     {48, 16384, 36, 6, 4, 17, {{1 << 18, 22, 1, 4}, {1 << 17, 9, 1, 12}}}},
 };
 
 inline bool tl_by_columns(bool backward, int dtype, int64_t M, int32_t T, int32_t k, int32_t d)
@@ -129,8 +138,9 @@ inline bool tl_by_columns(bool backward, int dtype, int64_t M, int32_t T, int32_
     if (T > kTlColsMaxT)
         return false;
     const TlColumnsRule& r = kTlColumnsRule[backward ? 1 : 0][dtype];
-    if (k >= r.high_k && T >= (int64_t)r.high_steps * d && M >= r.high_cols)
-        return false;
+    for (const auto& many : r.many)
+        if (M >= many.cols && k >= many.k && T >= many.t && T >= (int64_t)many.steps * d)
+            return false;
     if (k > r.max_k || T < (int64_t)r.steps * d)
         return true;
     return M <= r.few_cols ? T < r.few_t : 2 * T < r.t0 + (int64_t)r.per_d * d;

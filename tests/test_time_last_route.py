@@ -65,6 +65,8 @@ def routes(tmp_path_factory):
     ((64, 16, 64, 256, 8, 1, "bf16"), False, False),     # 30, 21 and 93, 69
     ((32, 16, 64, 512, 8, 1, "f32"), None, False),       # 90, 68
     ((40, 16, 64, 409, 4, 2, "q8_8"), None, False),      # 1.6 times
+    ((64, 16, 64, 256, 16, 2, "f32"), False, False),     # 44, 28 and 171, 95
+    ((40, 16, 64, 6, 16, 3, "f32"), None, True),         # few columns: 31, 38
     ((65, 16, 64, 252, 8, 33, "bf16"), False, False),    # no columns above 64 steps
 ])
 def test_measured_calls_go_to_the_faster_kernels(routes, call, fwd, bwd):
