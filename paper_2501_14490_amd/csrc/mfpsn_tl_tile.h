@@ -20,6 +20,7 @@
 namespace mfpsn {
 
 constexpr int kTileLdsMax = 65536;     // most LDS bytes of one wave's tile
+constexpr int kTileMinSeg = 256;       // shortest segment of columns split for lack of them
 constexpr int kTileMaxSpan = 1024;     // longest history (k-1) d of the segment tiles
 
 struct TileGeom {
@@ -55,7 +56,8 @@ struct TileGeom {
 // the usual d = 1, 2, 4, for at most one step in 24 more.
 MFPSN_TILE_FN int tile_chunk(const TileGeom& g, int W)
 {
-    const int R = (int)((((int64_t)W + g.d - 1) / g.d + g.m - 1) / g.m);
+    const uint32_t d = (uint32_t)g.d, m = (uint32_t)g.m;
+    const int R = (int)((((uint32_t)W + d - 1) / d + m - 1) / m);
     return R >= 24 ? R | 1 : R;
 }
 
@@ -204,12 +206,25 @@ inline bool tile_plan(TileGeom& g, int T, int N, int C, int S, int k, int dilati
             found = true;
         }
     }
-    if (!found) {
+    // few long columns: segments down to kTileMinSeg steps, so that one wave per
+    // SIMD has work (not more than the backward's slots allow waves).  64 columns
+    // of 2000 steps, f32 k = 8, forward and backward us: two segments 8.0, 22.7,
+    // seven 5.5, 13.7; from 960 columns on the longer segments win (k = 32, T =
+    // 700: backward 29.9 us whole, 37.6 in two).
+    const int64_t M = (int64_t)N * C * S, least = span > kTileMinSeg ? span : kTileMinSeg;
+    int64_t few = M <= 512 ? (1024 + M - 1) / M : 1;
+    if (slots >= 0 && few > (slots - C + 1) / M)
+        few = (slots - C + 1) / M;
+    if (few > T / least)
+        few = T / least;
+    if (span > kTileMaxSpan)
+        few = 1;
+    if (!found || few > 1) {
         // segments of one column: at least as long as the history, and long
         // enough that the history computed twice (backward) is a small share
         if (span > kTileMaxSpan || T < 2)
             return false;
-        if (span >= T) {
+        if (!found && span >= T) {
             // a column no longer than its history makes one segment: whole, in
             // a larger tile (at most 24 T bytes, T <= 1024)
             g.G = 1;
@@ -231,6 +246,7 @@ inline bool tile_plan(TileGeom& g, int T, int N, int C, int S, int k, int dilati
         const int64_t top = span > 512 || backward ? 2048 : 1024;
         int64_t n = (T + top - 1) / top;
         n = n > 2 ? n : 2;
+        n = n > few ? n : few;
         g.seg = (int32_t)((T + n - 1) / n);
         if (g.seg < span)
             g.seg = (int32_t)span;

@@ -384,6 +384,13 @@ __device__ __forceinline__ void unstage_h(const TileGeom& g, const V* img, int o
         one(t0 + lane);
 }
 
+// a / b, with a 32-bit division where both fit one (most of a tile's start on few
+// columns was 64-bit divisions)
+__device__ __forceinline__ int64_t divide(int64_t a, int64_t b)
+{
+    return ((uint64_t)(a | b) >> 32) == 0 ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b;
+}
+
 // The tiles of a wave in turn: columns col0 .. col0 + rows - 1 of group p,
 // steps from t0 (all wave-uniform; the divisions are done once)
 struct Cursor {
@@ -403,7 +410,7 @@ struct Cursor {
     }
     __device__ __forceinline__ Cursor(const TileGeom& g, int64_t q)
     {
-        p = (int)(q / g.Z);
+        p = (int)divide(q, g.Z);
         const uint32_t z = (uint32_t)(q - (int64_t)p * g.Z), per = (uint32_t)(g.sblk * g.nseg);
         n = (int)(z / per);
         const uint32_t rest = z - (uint32_t)n * per;
@@ -433,16 +440,15 @@ struct Cursor {
 };
 
 // The lane's part of a window of W steps: class steps [j0, j1) of class r
-// (times r + j d, from the window's start), L steps in the class
+// (times r + j d, from the window's start), L steps in the class; R = tile_chunk(g, W)
 struct Part {
     int r, j0, j1, L;
 };
-__device__ __forceinline__ Part part_of(const TileGeom& g, int W, int r, int chunk)
+__device__ __forceinline__ Part part_of(const TileGeom& g, int W, int r, int chunk, int R)
 {
-    const int R = tile_chunk(g, W);
     Part a;
     a.r = r;
-    a.L = r < W ? (W - r + g.d - 1) / g.d : 0;
+    a.L = r < W ? (int)((uint32_t)(W - r + g.d - 1) / (uint32_t)g.d) : 0;
     a.j0 = min(chunk * R, a.L);
     a.j1 = min(a.j0 + R, a.L);
     return a;
@@ -494,13 +500,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 
         v_th = a.v_th_q;
     int cur = -1, cur_W = -1, top = 0;
     const int ch = q / g.ncls, r0 = q - ch * g.ncls;  // (ch 0 when a row has more classes than lanes)
-    const int N = (int)(a.M / ((int64_t)g.S * g.C));
+    const int N = (int)divide(a.M, (int64_t)g.S * g.C);
     Part part{};
     Cursor tl(g, t);
     for (; t < tend; ++t, tl.next(g, N)) {
         if (tl.p != cur) {
             cur = tl.p;
-            const int c = g.by_channel ? cur : (int)(((int64_t)cur * g.G + min(row, tl.rows - 1)) / g.S);
+            const int c = g.by_channel ? cur : (int)divide((int64_t)cur * g.G + min(row, tl.rows - 1), g.S);
             taps.load(a.sign, a.shift, c, a.shift_lo, a.shift_hi);
             if constexpr (kF) {
                 const float b = ((const float*)a.bias)[c];
@@ -512,8 +518,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 
         const int W = min(g.seg, g.T - tl.t0);        // steps of the tile
         if (W != cur_W) {  // (the same for every tile but a column's last)
             cur_W = W;
-            part = part_of(g, W, r0, ch);
             top = tile_chunk(g, W);
+            part = part_of(g, W, r0, ch, top);
         }
         const int before = min(g.span, tl.t0);        // history staged before them
         const int count = g.nseg == 1 ? tl.rows * g.T : before + W;
@@ -583,7 +589,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 16 ? 4 
                     walk(std::false_type{}, pt);
                 if (g.ncls <= 64 || (r += 64) >= g.ncls)
                     break;
-                pt = part_of(g, W, r, 0);
+                pt = part_of(g, W, r, 0, top);
             }
         }
         wave_sync();
@@ -644,7 +650,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 8 ? 4 :
     int cur = -1, cur_rows = 0, cur_own = -1, cur_win = -1, top1 = 0, top2 = 0;
     int64_t cur_z = 0;  // the first tile of group cur this wave meets
     const int ch = q / g.ncls, r0 = q - ch * g.ncls;  // (ch 0 when a row has more classes than lanes)
-    const int N = (int)(a.M / ((int64_t)g.S * g.C));
+    const int N = (int)divide(a.M, (int64_t)g.S * g.C);
     Part part1{}, part2{};
     // the sums of the lanes of each channel of group `cur`, to its slots
     auto flush = [&]() __attribute__((always_inline)) {
@@ -693,7 +699,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 8 ? 4 :
             cur = tl.p;
             cur_z = tl.z(g);
             cur_rows = tl.rows;
-            const int c = g.by_channel ? cur : (int)(((int64_t)cur * g.G + min(row, tl.rows - 1)) / g.S);
+            const int c = g.by_channel ? cur : (int)divide((int64_t)cur * g.G + min(row, tl.rows - 1), g.S);
             taps.load(a.sign, a.shift, c, a.shift_lo, a.shift_hi);
             if constexpr (kF) {
                 const float b = ((const float*)a.bias)[c];
@@ -709,10 +715,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 8 ? 4 :
         if (own != cur_own || win != cur_win) {  // (the same for every tile but a column's last)
             cur_own = own;
             cur_win = win;
-            part1 = part_of(g, win, r0, ch);
-            part2 = part_of(g, own, r0, ch);
             top1 = tile_chunk(g, win);
             top2 = tile_chunk(g, own);
+            part1 = part_of(g, win, r0, ch, top1);
+            part2 = part_of(g, own, r0, ch, top2);
         }
         const int64_t e0 = tl.col0 * g.T + tl.t0;
         ExactCheck chk;
@@ -816,7 +822,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 8 ? 4 :
                     walk1(std::false_type{}, pt);
                 if (g.ncls <= 64 || (r += 64) >= g.ncls)
                     break;
-                pt = part_of(g, win, r, 0);
+                pt = part_of(g, win, r, 0, top1);
             }
         }
         wave_sync();
@@ -865,8 +871,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 8 ? 4 :
                     walk2(std::false_type{}, pt, Lw);
                 if (g.ncls <= 64 || (r += 64) >= g.ncls)
                     break;
-                pt = part_of(g, own, r, 0);
-                Lw = part_of(g, win, r, 0).L;
+                pt = part_of(g, own, r, 0, top2);
+                Lw = part_of(g, win, r, 0, top1).L;
             }
         }
         wave_sync();

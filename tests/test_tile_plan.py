@@ -42,6 +42,8 @@ int one(int T, int N, int C, int S, int k, int d, int es, int kind, long residen
     CHECK(g.lds <= 65536 && g.lds_x < g.lds && g.lds_x % 16 == 0 && g.G * g.Q <= 64 && g.G >= 1);
     const long waves = tile_waves(g, resident, slots);
     CHECK(waves >= 1);
+    if (M <= 512 && !bwd && T >= 512 && span <= 256)  // few long columns are cut, for more waves
+        CHECK(g.nseg >= std::min(T / 256, (int)(1024 / M)));
     const long chunk = (g.tiles + waves - 1) / waves;
     const int os = kind > 0 ? 4 : 1, v = 16 / es;
     std::vector<unsigned char> seen(M * T, 0);
@@ -153,7 +155,7 @@ EDGES = [(1, 1, 1, 1, 1, 1), (2, 1, 3, 1, 2, 5), (64, 1, 100, 1, 8, 1), (64, 1, 
          (250, 3, 70, 1, 16, 4), (30, 1, 3, 1936, 8, 3), (48, 1, 1000, 3, 2, 3), (1300, 1, 2, 1, 32, 8),
          (2049, 1, 2, 1, 32, 33), (4096, 1, 3, 1, 2, 1024), (5000, 1, 1, 2, 33 - 1, 33), (300, 1, 2, 2, 1, 500),
          (2100, 1, 1, 2, 3, 512), (1500, 2, 1, 3, 2, 1400), (100, 2, 3, 5, 2, 99),
-         (900, 2, 3, 1, 2, 1000), (1020, 1, 2, 1, 2, 1024)]
+         (900, 2, 3, 1, 2, 1000), (1020, 1, 2, 1, 2, 1024), (2000, 4, 4, 1, 8, 1), (700, 1, 3, 5, 16, 16)]
 
 
 @pytest.fixture(scope="module")

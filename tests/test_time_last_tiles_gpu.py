@@ -43,6 +43,7 @@ def place(t, offset):
     (150, 2, 3, 2, 2, 100, 0),    # more classes than lanes
     (70, 1, 4, 3, 4, 300, 0),     # dilation past the end
     (4100, 1, 2, 1, 4, 3, 0),     # segments, ragged tail
+    (2000, 2, 3, 1, 8, 1, 0),     # few columns: short segments
     (5003, 1, 1, 2, 2, 1000, 0),  # long history between segments, more classes than lanes
     (2, 3, 70, 1, 32, 1, 0),      # two steps, the highest order
     (900, 2, 3, 1, 2, 1000, 0),   # a dilation past the end of a column too long for 20 KB
