@@ -42,6 +42,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <type_traits>
 #include <utility>
 
@@ -945,32 +946,37 @@ __global__ __launch_bounds__(64 * kFinWaves) void tile_fin_kernel(const W* part,
 }
 
 // Waves of `kern` with `lds` bytes each that fit on the current device at
-// once: by registers (asked once per kernel and device) and by LDS
-template <typename Kern> int64_t resident_waves(Kern kern, int (&cache)[2][16], int lds)
+// once: by registers (asked once per kernel and device: blocks per CU and CUs
+// in one word, so that threads making a kernel's first calls see both or
+// neither; 0: not asked yet) and by LDS
+using WaveCache = std::atomic<uint32_t>[64];
+template <typename Kern> int64_t resident_waves(Kern kern, WaveCache& cache, int lds)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0)
         dev = 0;
-    const int s = dev & 15;
-    if (cache[0][s] == 0) {
+    uint32_t known = dev < 64 ? cache[dev].load(std::memory_order_relaxed) : 0;
+    if (known == 0) {
         int per = 0, cus = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, 64, 0) != hipSuccess || per < 1)
             per = 1;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
             cus = 1;
-        cache[1][s] = cus;
-        cache[0][s] = per;
+        known = (uint32_t)per << 16 | (uint32_t)(cus < 0xFFFF ? cus : 0xFFFF);
+        if (dev < 64)
+            cache[dev].store(known, std::memory_order_relaxed);
     }
-    const int fit = 163840 / ((lds + 1279) / 1280 * 1280);
-    const int per = cache[0][s] < fit ? cache[0][s] : fit;
-    return (int64_t)per * cache[1][s];
+    const int fit = 163840 / ((lds + 1279) / 1280 * 1280), per = (int)(known >> 16);
+    return (int64_t)(per < fit ? per : fit) * (known & 0xFFFFu);
 }
 
 template <int DT, int K, bool WANT_H> hipError_t fwd_tiles(const TlArgs& a, const TileGeom& g, hipStream_t st)
 {
-    static int cache[2][16];
+    static WaveCache cache;
     auto kern = tile_fwd_kernel<DT, K, WANT_H>;
     const int64_t waves = tile_waves(g, resident_waves(kern, cache, g.lds), -1);
+    if (waves < 1)
+        return hipErrorInvalidValue;
     const int64_t chunk = (g.tiles + waves - 1) / waves;
     const unsigned blocks = (unsigned)((g.tiles + chunk - 1) / chunk);
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(64), (size_t)g.lds, st, a, g, chunk);
@@ -979,7 +985,7 @@ template <int DT, int K, bool WANT_H> hipError_t fwd_tiles(const TlArgs& a, cons
 
 template <int DT, int K> hipError_t bwd_tiles(TlBwdArgs& a, const TileGeom& g, int64_t slots, hipStream_t st)
 {
-    static int cache[2][16];
+    static WaveCache cache;
     auto kern = tile_bwd_kernel<DT, K>;
     const int64_t waves = tile_waves(g, resident_waves(kern, cache, g.lds), slots);
     if (waves < 1)
