@@ -444,10 +444,11 @@ class StreamState:
 # Orders up to which the autograd functions let the backward recompute the
 # surrogate factor from x instead of saving it (4 bytes per element written by
 # the forward and read back).  Forward + backward on MI355X, recompute / saved,
-# at orders 8, 12, 16, 24: f32 planes [30,16,64,44,44] 0.70, 0.83, 0.88, 1.03
-# and channels [250,128,512] 0.76, 0.83, 1.04, 1.15 (0.93 at order 16 where the
-# tensors leave the last-level cache, [250,256,512]); bf16 0.70, 0.94, 0.97,
-# 1.06 and 0.85, 0.87, 1.20, 1.14.
+# over nine shapes of 0.4 M to 67 M elements and d = 1, 3, worst (average): f32
+# up to order 14 0.996 (0.80), 15 1.11 (0.92, planes of 44x44 alone lose), 16
+# 0.996 (0.89), 18 to 24 1.22 (0.99); bf16 up to order 10 1.004 (0.82), 11 and 12
+# 1.10 (0.93, [16,64,128,256] and [2048,32,128] lose), 13 and 14 1.13 (0.97), 15
+# to 24 1.26 (1.03).
 RECOMPUTE_MAX_K = {MFPSN_F32: 16, MFPSN_BF16: 12}
 
 
