@@ -274,10 +274,8 @@ int mfpsn_forward_time_last(const mfpsn_desc* desc, const void* x, const int8_t*
     a.S = desc->S;
     a.k = desc->k;
     a.d = desc->dilation;
-    // tl_fwd_kernel (histories no tile holds): segments of 256 time steps, or
-    // of 64 for short sequences (fewer idle lanes)
-    a.steps_per_lane = desc->T > 96 ? 4 : 1;
-    a.nseg = (int32_t)(((int64_t)desc->T + 64 * a.steps_per_lane - 1) / (64 * a.steps_per_lane));
+    // tl_fwd_kernel (where no tile holds the history)
+    a.nseg = (int32_t)(((int64_t)desc->T + 64 * kTlSteps - 1) / (64 * kTlSteps));
     a.halo = span <= kTlMaxHalo ? (int32_t)span : 0;
     a.shift_lo = desc->shift_lo;
     a.shift_hi = desc->shift_hi;

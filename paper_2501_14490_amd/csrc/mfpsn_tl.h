@@ -13,6 +13,7 @@ namespace mfpsn {
 
 constexpr int kTlWaves = 4;                 // waves per block
 constexpr int kTlMaxHalo = 2048;            // longest history tl_fwd_kernel stages in LDS
+constexpr int kTlSteps = 4;                 // steps per lane of its segments
 constexpr int kTlColsMaxT = 64;             // longest column of the lane-per-column kernels
 // What sizes the backward's workspace (tl_bwd_slots)
 constexpr int kTlSeg = 256;                 // steps per counted segment of columns above kTlColsMaxT
@@ -28,8 +29,7 @@ struct TlArgs {
     void* h_out;            // nullable, float or int32 [N][C][S][T]
     int64_t M;              // columns, N*C*S
     int32_t T, C, S, k, d;
-    int32_t steps_per_lane; // tl_fwd_kernel: 1 or 4: segments of 64 or 256 time steps
-    int32_t nseg;           // tl_fwd_kernel: segments per column, ceil(T / (64 * steps_per_lane))
+    int32_t nseg;           // tl_fwd_kernel: segments of 64 kTlSteps steps per column
     int32_t halo;           // tl_fwd_kernel: LDS history slots per wave (0: taps read from global memory)
     int32_t shift_lo, shift_hi;
     float v_th;

@@ -74,12 +74,12 @@ struct TlUnit {
 // consecutive addresses), the first NS+2 loads of the next segment's window
 // in flight while the current one computes; without LDS (histories above
 // kTlMaxHalo) the taps read global memory.
-template <int DT, int K, int NS, bool LDS>
+template <int DT, int K, bool LDS>
 __global__ __launch_bounds__(kTlWaves * 64) void tl_fwd_kernel(TlArgs a)
 {
     using V = typename TlIO<DT>::V;
     constexpr bool kF = DT != MFPSN_Q8_8;
-    constexpr int kW = 64 * NS, kStage = NS + 2;
+    constexpr int NS = kTlSteps, kW = 64 * NS, kStage = NS + 2;
     extern __shared__ uint32_t tl_lds[];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
     const int64_t units = a.M * a.nseg, stride = (int64_t)gridDim.x * kTlWaves;
@@ -902,11 +902,11 @@ __global__ __launch_bounds__(64) void tl_bwd_reduce_kernel(const W* part, void* 
         ((O*)grad_b)[c] = (O)v;
 }
 
-template <int DT, int K, int NS, bool LDS>
+template <int DT, int K, bool LDS>
 void launch_variant(const TlArgs& a, hipStream_t st)
 {
-    constexpr int kW = 64 * NS;
-    auto kern = tl_fwd_kernel<DT, K, NS, LDS>;
+    constexpr int kW = 64 * kTlSteps;
+    auto kern = tl_fwd_kernel<DT, K, LDS>;
     const size_t lds = LDS ? (size_t)kTlWaves * (kW + a.halo) * 4 : 0;
     // persistent grid: every resident block slot of the device, at most one
     // segment per wave
@@ -930,17 +930,13 @@ void launch_variant(const TlArgs& a, hipStream_t st)
 template <int DT, int K>
 void launch_k(const TlArgs& a, hipStream_t st)
 {
-    const bool lds = a.halo > 0 || (K - 1) * a.d == 0;
-    const bool short_steps = a.steps_per_lane == 1;
-    if (lds)
-        short_steps ? launch_variant<DT, K, 1, true>(a, st) : launch_variant<DT, K, 4, true>(a, st);
-    else
-        short_steps ? launch_variant<DT, K, 1, false>(a, st) : launch_variant<DT, K, 4, false>(a, st);
+    a.halo > 0 ? launch_variant<DT, K, true>(a, st) : launch_variant<DT, K, false>(a, st);
 }
+// (order 1 has no history: always tiles or columns)
 template <int DT, int LO, int... Ks>
 void long_fwd(const TlArgs& a, hipStream_t st, std::integer_sequence<int, Ks...>)
 {
-    (void)((a.k == LO + Ks ? (launch_k<DT, LO + Ks>(a, st), true) : false) || ...);
+    (void)((a.k == LO + Ks && a.k > 1 ? (launch_k<DT, (LO + Ks > 1 ? LO + Ks : 2)>(a, st), true) : false) || ...);
 }
 
 template <int DT, int LO, int... Ks>
