@@ -61,6 +61,8 @@
 extern "C" {
 #endif
 
+/* Raised when an existing entry point or structure changes; entry points that
+ * are added leave it. */
 #define MFPSN_ABI_VERSION 10
 #define MFPSN_MAX_K 32
 
