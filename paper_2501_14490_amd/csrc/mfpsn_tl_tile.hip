@@ -23,13 +23,13 @@
 // Waves take contiguous runs of tiles that share channels, so taps and
 // grad_w sums stay in registers, and the sums are reduced once per run.
 //
-// Measured on MI355X (forward + backward, us), against a lane per
-// column of a transposed tile up to T = 64 and a lane per time step of a segment
-// above, which read k values from LDS per step:
-// f32 [32,128,256,32] k = 8 207 -> 158, f32 [250,256,512] k = 16 d = 2
-// 569 -> 236, Q8.8 [4096,16,1024] k = 32 d = 4 1648 -> 743.  The backward
-// issues 88 to 150 VALU instructions per 64 elements at orders 8 and 16 and
-// keeps the VALUs about 85% busy; LDS bank conflicts are below 2% of the time.
+// Measured on MI355X (forward + backward, us), against a lane per column of a
+// transposed tile up to T = 64 and a lane per time step of a segment above, which
+// read k values from LDS per step: f32 [32,128,256,32] k = 8 208 -> 152 (its
+// forward, 25, by columns), f32 [250,256,512] k = 16 d = 2 570 -> 235, Q8.8
+// [4096,16,1024] k = 32 d = 4 1655 -> 733.  The backward issues 88 to 150 VALU
+// instructions per 64 elements at orders 8 and 16 and keeps the VALUs about 85%
+// busy; LDS bank conflicts are below 2% of the time.
 // Short columns go to tiles only where they are faster (tl_by_columns): a lane
 // takes one class, so a tile has at most 64 / d columns, whose start costs as
 // much as the few steps of a short one.
