@@ -392,7 +392,8 @@ int mfpsn_backward_time_last(const mfpsn_desc* desc, const void* x, const void* 
                 g.Z >= (int64_t)1 << 31)
                 return MFPSN_ERR_SHAPE;  // (a plan exists for every accepted call; Z: more elements than any memory
                                          // holds)
-            cols = desc->T <= kTlColsMaxT && tile_short_of_waves(g, desc->k, slots);
+            cols = !tl_bears_few_waves(desc->dtype, desc->T, desc->k, desc->dilation) &&
+                   tile_short_of_waves(g, desc->k, slots);
         }
         if (cols) {
             a.vec_x = aligned(x, 4 * es) && aligned(grad_spikes, 4 * es) ? 1 : 0;

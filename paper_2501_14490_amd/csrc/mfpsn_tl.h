@@ -114,23 +114,24 @@ struct TlColumnsRule {
     int32_t t0, per_d;  // more: from (t0 + per_d d) / 2 steps
     int32_t steps;      // and with as many steps per residue class
     int32_t max_k;      // up to this order
-    // of many columns (at least cols) also those of order k and more from t
-    // steps, with as many as `steps` per class
+    // of many columns (at least cols) also these orders and lengths, with as
+    // many as `steps` per class (max_k 0: none)
     struct {
-        int64_t cols;
-        int32_t k, t, steps;
-    } many[2];
+        int32_t cols, min_k, max_k, min_t, max_t, steps;
+    } many[6];
 };
-constexpr int64_t kTlNone = INT64_MAX;  // no number of columns
 constexpr TlColumnsRule kTlColumnsRule[2][3] = {
     // forward: f32, bf16, Q8.8
-    {{30, 32768, 84, 4, 4, 32, {{kTlNone, 1, 1, 1}, {kTlNone, 1, 1, 1}}},
-     {32, 49152, 108, 5, 4, 25, {{1 << 20, 30, 1, 6}, {kTlNone, 1, 1, 1}}},
-     {28, 32768, 80, 12, 3, 22, {{1 << 18, 32, 1, 4}, {kTlNone, 1, 1, 1}}}},
+    {{30, 32768, 84, 4, 4, 32, {{1 << 17, 2, 16, 40, 64, 12}, {1 << 17, 22, 32, 40, 64, 7}}},
+     {32, 49152, 108, 5, 4, 25, {{1 << 20, 30, 32, 1, 64, 6}}},
+     {28, 32768, 80, 12, 3, 22, {{1 << 18, 32, 32, 1, 64, 4}, {1 << 17, 2, 12, 40, 64, 14}}}},
     // backward
-    {{36, 6553, 48, 6, 5, 14, {{1 << 17, 26, 1, 8}, {1 << 17, 9, 40, 8}}},
-     {48, 6553, 96, 4, 4, 16, {{1 << 17, 26, 1, 6}, {kTlNone, 1, 1, 1}}},
-     {48, 16384, 36, 6, 4, 17, {{1 << 18, 22, 1, 4}, {1 << 17, 9, 1, 12}}}},
+    {{36, 6553, 48, 6, 5, 14, {{1 << 17, 26, 32, 1, 64, 8}, {1 << 17, 9, 32, 40, 64, 8}, {1 << 19, 26, 32, 4, 32, 3},
+                               {1 << 15, 2, 11, 28, 64, 5}, {1 << 18, 18, 32, 4, 24, 6}, {1 << 15, 2, 16, 40, 64, 6}}},
+     {48, 6553, 96, 4, 4, 16, {{1 << 17, 26, 32, 1, 64, 6}, {1 << 19, 26, 32, 4, 24, 2}, {1 << 18, 16, 24, 4, 24, 6},
+                               {1 << 15, 12, 16, 20, 40, 14}, {1 << 15, 26, 32, 40, 64, 2}}},
+     {48, 16384, 36, 6, 4, 17, {{1 << 18, 22, 32, 1, 64, 4}, {1 << 17, 9, 32, 1, 64, 12}, {1 << 15, 18, 32, 40, 64, 2},
+                                {1 << 19, 22, 32, 4, 16, 2}, {1 << 17, 22, 32, 20, 64, 2}, {1 << 20, 12, 20, 4, 16, 3}}}},
 };
 
 inline bool tl_by_columns(bool backward, int dtype, int64_t M, int32_t T, int32_t k, int32_t d)
@@ -139,11 +140,21 @@ inline bool tl_by_columns(bool backward, int dtype, int64_t M, int32_t T, int32_
         return false;
     const TlColumnsRule& r = kTlColumnsRule[backward ? 1 : 0][dtype];
     for (const auto& many : r.many)
-        if (M >= many.cols && k >= many.k && T >= many.t && T >= (int64_t)many.steps * d)
+        if (M >= many.cols && k >= many.min_k && k <= many.max_k && T >= many.min_t && T <= many.max_t &&
+            T >= (int64_t)many.steps * d)
             return false;
     if (k > r.max_k || T < (int64_t)r.steps * d)
         return true;
     return M <= r.few_cols ? T < r.few_t : 2 * T < r.t0 + (int64_t)r.per_d * d;
+}
+
+// Whether a short tile backward is worth it although its slots of partial sums
+// keep it from waves that fit (tile_short_of_waves): f32 and Q8.8 columns of 42
+// steps and more at orders up to 12 take 0.71 of the columns' time (of 450 calls
+// the worst 1.1), others 1.0 to 1.7.
+inline bool tl_bears_few_waves(int dtype, int32_t T, int32_t k, int32_t d)
+{
+    return T > kTlColsMaxT || (dtype != 1 && T >= 42 && T >= (int64_t)4 * d && k <= 12);
 }
 
 // The lane-per-column kernels (mfpsn_tl.hip, T <= kTlColsMaxT).  The backward

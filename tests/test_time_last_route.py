@@ -28,7 +28,7 @@ int main()
         const long M = (long)N * C * S, slots = tl_bwd_slots(M, T, C, N, (long)(k - 1) * d);
         bool bwd = tl_by_columns(true, dt, M, T, k, d);
         TileGeom g;
-        if (!bwd && tile_plan(g, T, N, C, S, k, d, dt == 0 ? 4 : 2, slots) && T <= kTlColsMaxT)
+        if (!bwd && tile_plan(g, T, N, C, S, k, d, dt == 0 ? 4 : 2, slots) && !tl_bears_few_waves(dt, T, k, d))
             bwd = tile_short_of_waves(g, k, slots);
         printf("%d %d %d\n", tl_by_columns(false, dt, M, T, k, d), bwd,
                !bwd || (M + 63) / 64 - 1 + ((long)N * C - 1) < slots);
@@ -67,6 +67,9 @@ def routes(tmp_path_factory):
     ((40, 16, 64, 409, 4, 2, "q8_8"), None, False),      # 1.6 times
     ((64, 16, 64, 256, 16, 2, "f32"), False, False),     # 44, 28 and 171, 95
     ((40, 16, 64, 6, 16, 3, "f32"), None, True),         # few columns: 31, 38
+    ((30, 16, 64, 546, 16, 2, "bf16"), None, False),     # many of a high order: 112, 78
+    ((64, 16, 64, 30, 8, 4, "f32"), None, False),        # fewer waves than fit, and still faster
+    ((64, 16, 64, 30, 8, 4, "bf16"), None, True),        # and not
     ((65, 16, 64, 252, 8, 33, "bf16"), False, False),    # no columns above 64 steps
 ])
 def test_measured_calls_go_to_the_faster_kernels(routes, call, fwd, bwd):
