@@ -103,35 +103,43 @@ hipError_t tile_backward(TlBwdArgs& a, const TileGeom& g, int64_t slots, hipStre
 // small or lanes scarce, and the column backward loses most of its waves to
 // registers at high orders.  Fitted on MI355X to 9615 calls of both kernels (T
 // 1 to 64, all orders, d 1 to 32, 2^16 to 2^24 elements): the forwards that go
-// to tiles (2089) are 1.34 times faster there on average, the backwards (2881)
-// 1.54 times, and the worst of them 1.16 and 1.09 times slower.  Columns /
-// tiles, us, 2^24 elements, k = 8: bf16 T = 30, d = 1, 3 forward 19, 20 / 20,
-// 27, backward 69, 68 / 63, 77; bf16 T = 64, d = 1 30 / 21 and 93 / 69; f32 T =
-// 32, d = 1 24 / 24 and 90 / 68.
+// to tiles (2583) take 0.76 of the columns' time on average, the backwards (4244)
+// 0.67, and the worst of them 1.15 and 1.17.  Columns / tiles, us, 2^24 elements,
+// k = 8: bf16 T = 30, d = 1, 3 forward 19, 20 / 20, 27, backward 69, 68 / 63, 77;
+// bf16 T = 64, d = 1 30 / 21 and 93 / 69; f32 T = 32, d = 1 24 / 24 and 90 / 68.
+// 512 columns of 64 steps, f32 k = 16 backward 39 / 17.
 struct TlColumnsRule {
     int32_t few_t;      // few columns (at most few_cols): tiles from this length
     int64_t few_cols;
     int32_t t0, per_d;  // more: from (t0 + per_d d) / 2 steps
     int32_t steps;      // and with as many steps per residue class
     int32_t max_k;      // up to this order
-    // of many columns (at least cols) also these orders and lengths, with as
-    // many as `steps` per class (max_k 0: none)
+    // and these numbers of columns, orders and lengths, with as many as `steps`
+    // per class (max_k 0: none)
     struct {
-        int32_t cols, min_k, max_k, min_t, max_t, steps;
-    } many[6];
+        int32_t min_cols, max_cols, min_k, max_k, min_t, max_t, steps;
+    } also[8];
 };
+constexpr int32_t kTlMany = INT32_MAX;  // no upper limit of columns
 constexpr TlColumnsRule kTlColumnsRule[2][3] = {
     // forward: f32, bf16, Q8.8
-    {{30, 32768, 84, 4, 4, 32, {{1 << 17, 2, 16, 40, 64, 12}, {1 << 17, 22, 32, 40, 64, 7}}},
-     {32, 49152, 108, 5, 4, 25, {{1 << 20, 30, 32, 1, 64, 6}}},
-     {28, 32768, 80, 12, 3, 22, {{1 << 18, 32, 32, 1, 64, 4}, {1 << 17, 2, 12, 40, 64, 14}}}},
+    {{30, 32768, 84, 4, 4, 32, {{1 << 17, kTlMany, 2, 16, 40, 64, 12}, {1 << 17, kTlMany, 22, 32, 40, 64, 7}}},
+     {32, 49152, 108, 5, 4, 25, {{0, 32768, 2, 32, 28, 64, 2}, {1 << 20, kTlMany, 30, 32, 1, 64, 6}}},
+     {28, 32768, 80, 12, 3, 22, {{0, 32768, 18, 32, 20, 64, 2}, {1 << 18, kTlMany, 32, 32, 1, 64, 4},
+         {1 << 17, kTlMany, 2, 12, 40, 64, 14}}}},
     // backward
-    {{36, 6553, 48, 6, 5, 14, {{1 << 17, 26, 32, 1, 64, 8}, {1 << 17, 9, 32, 40, 64, 8}, {1 << 19, 26, 32, 4, 32, 3},
-                               {1 << 15, 2, 11, 28, 64, 5}, {1 << 18, 18, 32, 4, 24, 6}, {1 << 15, 2, 16, 40, 64, 6}}},
-     {48, 6553, 96, 4, 4, 16, {{1 << 17, 26, 32, 1, 64, 6}, {1 << 19, 26, 32, 4, 24, 2}, {1 << 18, 16, 24, 4, 24, 6},
-                               {1 << 15, 12, 16, 20, 40, 14}, {1 << 15, 26, 32, 40, 64, 2}}},
-     {48, 16384, 36, 6, 4, 17, {{1 << 18, 22, 32, 1, 64, 4}, {1 << 17, 9, 32, 1, 64, 12}, {1 << 15, 18, 32, 40, 64, 2},
-                                {1 << 19, 22, 32, 4, 16, 2}, {1 << 17, 22, 32, 20, 64, 2}, {1 << 20, 12, 20, 4, 16, 3}}}},
+    {{36, 6553, 48, 6, 5, 14, {{0, 4096, 2, 32, 8, 64, 12}, {0, 32768, 2, 24, 56, 64, 12},
+         {1 << 17, kTlMany, 26, 32, 1, 64, 8}, {1 << 17, kTlMany, 9, 32, 40, 64, 8},
+         {1 << 19, kTlMany, 26, 32, 4, 32, 3}, {1 << 15, kTlMany, 2, 11, 28, 64, 5},
+         {1 << 18, kTlMany, 18, 32, 4, 24, 6}, {1 << 15, kTlMany, 2, 16, 40, 64, 6}}},
+     {48, 6553, 96, 4, 4, 16, {{0, 32768, 2, 12, 8, 64, 12}, {0, 4096, 2, 32, 8, 64, 12},
+         {1 << 17, kTlMany, 26, 32, 1, 64, 6}, {1 << 19, kTlMany, 26, 32, 4, 24, 2},
+         {1 << 18, kTlMany, 16, 24, 4, 24, 6}, {1 << 15, kTlMany, 12, 16, 20, 40, 14},
+         {1 << 15, kTlMany, 26, 32, 40, 64, 2}}},
+     {48, 16384, 36, 6, 4, 17, {{0, 32768, 2, 12, 8, 64, 12}, {0, 4096, 2, 32, 20, 64, 2},
+         {1 << 18, kTlMany, 22, 32, 1, 64, 4}, {1 << 17, kTlMany, 9, 32, 1, 64, 12},
+         {1 << 15, kTlMany, 18, 32, 40, 64, 2}, {1 << 19, kTlMany, 22, 32, 4, 16, 2},
+         {1 << 17, kTlMany, 22, 32, 20, 64, 2}, {1 << 20, kTlMany, 12, 20, 4, 16, 3}}}},
 };
 
 inline bool tl_by_columns(bool backward, int dtype, int64_t M, int32_t T, int32_t k, int32_t d)
@@ -139,9 +147,9 @@ inline bool tl_by_columns(bool backward, int dtype, int64_t M, int32_t T, int32_
     if (T > kTlColsMaxT)
         return false;
     const TlColumnsRule& r = kTlColumnsRule[backward ? 1 : 0][dtype];
-    for (const auto& many : r.many)
-        if (M >= many.cols && k >= many.min_k && k <= many.max_k && T >= many.min_t && T <= many.max_t &&
-            T >= (int64_t)many.steps * d)
+    for (const auto& c : r.also)
+        if (M >= c.min_cols && M <= (c.max_cols == kTlMany ? M : c.max_cols) && k >= c.min_k && k <= c.max_k &&
+            T >= c.min_t && T <= c.max_t && T >= (int64_t)c.steps * d)
             return false;
     if (k > r.max_k || T < (int64_t)r.steps * d)
         return true;

@@ -66,6 +66,7 @@ def routes(tmp_path_factory):
     ((32, 16, 64, 512, 8, 1, "f32"), None, False),       # 90, 68
     ((40, 16, 64, 409, 4, 2, "q8_8"), None, False),      # 1.6 times
     ((64, 16, 64, 256, 16, 2, "f32"), False, False),     # 44, 28 and 171, 95
+    ((64, 1, 512, 1, 16, 1, "f32"), None, False),        # fewer columns yet: 39, 17
     ((40, 16, 64, 6, 16, 3, "f32"), None, True),         # few columns: 31, 38
     ((30, 16, 64, 546, 16, 2, "bf16"), None, False),     # many of a high order: 112, 78
     ((64, 16, 64, 30, 8, 4, "f32"), None, False),        # fewer waves than fit, and still faster
